@@ -65,6 +65,14 @@ enum {
  *   accumulation and 16-bit weights; activations enter those products as
  *   hi + lo 16-bit pairs (about 22 bits); tanh, the descriptor contractions,
  *   the remaining fitting layers and the output layer in FP32.
+ * An embedding net is a function of the one number s: under DP_FP64,
+ * DP_MIX_FP32 and DP_MIX_FP16 (embedding widths up to 128) dp_set_model lays
+ * the nets out as piecewise Chebyshev expansions, from the weights as the
+ * policy rounds them and below the rounding of its arithmetic (double under
+ * DP_FP64, FP32 otherwise), and evaluations sum those; the layers themselves
+ * are evaluated where a net has no such expansion, in frames with a pair
+ * closer than about 0.03 A (that evaluation then costs both), under
+ * DP_MIX_BF16, for wide nets and for the 16-bit student nets.
  * Coordinates, wrapping, distances, the environment matrix (before its
  * rounding), the force Jacobian, energy / force / virial sums and the
  * integrator stay double in every mode. */

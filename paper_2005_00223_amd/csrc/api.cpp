@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "dp_expand.h"
 #include "dp_internal.h"
 #include "dp_mix.h"
 #include "dp_wide.h"
@@ -186,6 +187,10 @@ struct Workspace {
   double *cell_part;
   // mixed-precision buffers
   float *T32, *dT32, *tbuf;
+  // expansion path: per-atom segment masks, H / M rows of `seg` segments
+  unsigned long long *exp_mask = nullptr;
+  void *exp_hm = nullptr;
+  int seg = 0;
   int prec = -1;  // precision the buffers were laid out for
   DevStatus *status;
 };
@@ -221,6 +226,12 @@ struct EmbNets {
   double tab_shi = 0.0;             // its range of s
   bool tab_ok = false;
   bool ready = false;
+  // Chebyshev expansions of the nets, in the real type of the precision in use
+  void *d_exp = nullptr;
+  size_t exp_cf = 0, exp_cb = 0;    // element offsets of the coefficient tables
+  int exp_P = 0;
+  double exp_smax = 0.0;
+  bool exp_ok = false;
 };
 
 struct dp_ctx {
@@ -275,6 +286,8 @@ struct dp_ctx {
     bool ok = false;   // the forward of this evaluation ran
   } wb;
   int pending_rc = DP_OK;  // an error inside an evaluation (reported by read_status)
+  bool exp_off = false;    // this call's frames hold a pair beyond the expansions: evaluate the layers
+  bool exp_now = false;    // the last forward ran on the expansions (its backward does too)
   int wide_split = 1;      // wide nets: activations stored as hi + lo 16-bit halves (0: one 16-bit value)
   // no-allocation entry point: the device address of this GPU's static
   // scratch array (NULL if its lookup failed, scratch_rc says why), the
@@ -333,7 +346,10 @@ inline bool prec_ok(int p) { return p == DP_FP64 || p == DP_MIX_FP32 || prec16(p
 // Lay every buffer of the workspace out in one block: returns the block's
 // size for nn atoms, nc cells and cc candidate slots per atom, and, when
 // base is not NULL, points the buffers of w into the block at base.
-size_t ws_carve(const dp_ctx *c, Workspace &w, int64_t nn, int64_t nc, int cc, bool nd, char *base) {
+// exp: with the buffers of the expansion path (its H / M rows take the place
+// of the environment rows, which it does not store, where those hold at
+// least EXP_SEG segments per atom).
+size_t ws_carve(const dp_ctx *c, Workspace &w, int64_t nn, int64_t nc, int cc, bool nd, char *base, bool exp) {
   const Dims &d = c->dims;
   const bool mixed = prec16(c->precision);
   const bool f32 = c->precision == DP_MIX_FP32;
@@ -363,9 +379,17 @@ size_t ws_carve(const dp_ctx *c, Workspace &w, int64_t nn, int64_t nc, int cc, b
   add((void **)&w.blk_counts, (size_t)4 * nblk * MAXT);
   add((void **)&w.type_count, 4 * MAXT);
   add((void **)&w.type_start, 4 * (MAXT + 1));
+  const size_t env0 = off;
   if (mixed || f32) add((void **)&w.rt32, sizeof(float4) * nn * d.nnei);
   else add((void **)&w.rt, sizeof(double4) * nn * d.nnei);
   if (!mixed) add((void **)&w.dr, sizeof(double4) * nn * d.nnei);
+  if (exp) {
+    const size_t per = (mixed || f32 ? sizeof(float) : sizeof(double)) * 2 * EXP_KP * 4;  // M of one segment
+    if (off - env0 < per * EXP_SEG * nn) add(&w.exp_hm, per * EXP_SEG * nn);
+    else if (base) w.exp_hm = base + env0;
+    w.seg = EXP_SEG;
+    add((void **)&w.exp_mask, sizeof(unsigned long long) * nn);
+  }
   if (!mixed) {
     // in float under DP_MIX_FP32 (the pointers are then read as float)
     add((void **)&w.T, rb * nn * d.M1 * 4);
@@ -434,13 +458,16 @@ int ensure_ws(dp_ctx *c, int64_t n, int64_t ncell, int cand_cap) {
     return DP_OK;
   if (c->noalloc) {
     Workspace nw{};
-    const size_t need = ws_carve(c, nw, n, ncell, cand_cap, need_nd, nullptr);
+    const size_t need = ws_carve(c, nw, n, ncell, cand_cap, need_nd, nullptr, false);
     if (need > NOALLOC_SCRATCH_BYTES)
       return fail(c, DP_E_CAP, "dp_compute_noalloc: this system needs a workspace of " + std::to_string(need) +
                                    " bytes, more than the " + std::to_string(NOALLOC_SCRATCH_BYTES) +
                                    "-byte static scratch holds (use dp_compute)");
+    // with the expansions' buffers where they fit beside the rest
+    const bool exp = ws_carve(c, nw, n, ncell, cand_cap, need_nd, nullptr, true) <= NOALLOC_SCRATCH_BYTES;
+    nw = Workspace{};
     nw.owned = false;
-    ws_carve(c, nw, n, ncell, cand_cap, need_nd, (char *)c->scratch);
+    ws_carve(c, nw, n, ncell, cand_cap, need_nd, (char *)c->scratch, exp);
     w = nw;
     c->cgrid_ok = false;
     return DP_OK;
@@ -452,13 +479,13 @@ int ensure_ws(dp_ctx *c, int64_t n, int64_t ncell, int cand_cap) {
   bool nd = need_nd || w.nd;
   free_ws(w);
   Workspace nw{};
-  const size_t off = ws_carve(c, nw, nn, nc, cc, nd, nullptr);
+  const size_t off = ws_carve(c, nw, nn, nc, cc, nd, nullptr, true);
   void *base = nullptr;
   if (hipMalloc(&base, off) != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, DP_E_OOM, "workspace allocation of " + std::to_string(off) + " bytes failed");
   }
-  ws_carve(c, nw, nn, nc, cc, nd, (char *)base);
+  ws_carve(c, nw, nn, nc, cc, nd, (char *)base, true);
   w = nw;
   c->cgrid_ok = false;
   return DP_OK;
@@ -697,6 +724,69 @@ int upload_mix(dp_ctx *c) {
   return DP_OK;
 }
 
+// Expansions of the nets of m (dp_expand.h) for the precision in use, with
+// the weights its layer kernels hold.  Nets without one leave exp_ok false.
+template <typename Real>
+int upload_exp_t(dp_ctx *c, const ExpTables &t, EmbNets &en) {
+  const int nets = en.d.ntypes * en.d.ntypes;
+  const size_t np = (size_t)nets * t.P, blk = (size_t)EXP_KP * t.M1p;
+  en.exp_cf = np * 4;
+  en.exp_cb = en.exp_cf + np * blk;
+  std::vector<Real> h(en.exp_cb + np * 2 * blk);
+  for (size_t q = 0; q < np; ++q) {
+    h[4 * q] = (Real)t.lo[q];
+    h[4 * q + 1] = (Real)t.mid[q];
+    h[4 * q + 2] = (Real)t.ih[q];
+    const double *C = t.C.data() + q * 2 * blk;
+    for (size_t k = 0; k < (size_t)EXP_KP; ++k)
+      for (size_t m = 0; m < (size_t)t.M1p; ++m) {
+        h[en.exp_cf + q * blk + k * t.M1p + m] = (Real)C[k * t.M1p + m];
+        h[en.exp_cb + q * 2 * blk + m * EXP_KP + k] = (Real)C[k * t.M1p + m];
+        h[en.exp_cb + (q * 2 + 1) * blk + m * EXP_KP + k] = (Real)C[blk + k * t.M1p + m];
+      }
+  }
+  HIPCHK(c, hipMalloc(&en.d_exp, sizeof(Real) * h.size()));
+  HIPCHK(c, hipMemcpy(en.d_exp, h.data(), sizeof(Real) * h.size(), hipMemcpyHostToDevice));
+  en.exp_P = t.P;
+  en.exp_smax = t.smax;
+  en.exp_ok = true;
+  return DP_OK;
+}
+
+int upload_exp(dp_ctx *c, const HostModel &m, EmbNets &en) {
+  if (en.d_exp) (void)hipFree(en.d_exp);
+  en.d_exp = nullptr;
+  en.exp_ok = false;
+  // BF16, wide nets and the 16-bit student nets keep their layer kernels:
+  // their results carry those kernels' own rounding (5e-5 and 1e-4 of the
+  // forces on copper), and callers' trajectories with it
+  const Dims &d = en.d;
+  if (c->precision == DP_MIX_BF16 || (c->precision == DP_MIX_FP16 && (en.wide || &en == &c->en[1]))) return DP_OK;
+  ExpTables t;
+  try {
+    std::vector<ExpNetIn> nets((size_t)d.ntypes * d.ntypes);
+    for (int k = 0; k < (int)nets.size(); ++k) {
+      ExpNetIn &n = nets[k];
+      n.n_layers = d.n_emb;
+      n.lin = d.emb_lin != 0;
+      for (int l = 0; l <= d.n_emb; ++l) n.w[l] = d.ew[l];
+      for (int l = 0; l < d.n_emb; ++l) {
+        n.W[l] = m.eW[(size_t)k * d.n_emb + l];
+        n.b[l] = m.eb[(size_t)k * d.n_emb + l];
+        if (c->precision == DP_FP64) continue;
+        for (auto &v : n.b[l]) v = (float)v;
+        for (auto &v : n.W[l]) v = c->precision == DP_MIX_FP16 && l > 0 ? st_round16((float)v, 0) : (double)(float)v;
+      }
+    }
+    const bool f64 = c->precision == DP_FP64;
+    t = exp_build(nets, d.ntypes, rup(d.M1, 16), f64 ? EXP_K64 : EXP_K32, f64, f64 ? 0x1p-52 : 0x1p-25);
+    if (!t.ok) return DP_OK;
+    return f64 ? upload_exp_t<double>(c, t, en) : upload_exp_t<float>(c, t, en);
+  } catch (const std::exception &) {
+    return DP_OK;  // out of host memory: the layer kernels evaluate the nets
+  }
+}
+
 // ---------------------------------------------------------------------------
 // one evaluation
 // ---------------------------------------------------------------------------
@@ -889,6 +979,45 @@ int64_t eval_rows(const dp_ctx *c, int64_t n) {
   return (n + ROW_TILE - 1) / ROW_TILE * ROW_TILE + (int64_t)ROW_TILE * c->dims.ntypes;
 }
 
+// Whether an evaluation of the active nets runs on their expansions.
+inline bool use_exp(const dp_ctx *c) { return c->en[c->active].exp_ok && !c->exp_off && c->ws.exp_hm; }
+
+template <typename Real>
+ExpArgs<Real> exp_args(dp_ctx *c, int64_t rows, double *F) {
+  Workspace &w = c->ws;
+  const EmbNets &en = c->en[c->active];
+  ExpArgs<Real> a{};
+  a.d = en.d;
+  a.tab.P = en.exp_P;
+  a.tab.M1p = rup(en.d.M1, 16);
+  a.tab.smax = (Real)en.exp_smax;
+  a.tab.piece = (const Real *)en.d_exp;
+  a.tab.Cf = (const Real *)en.d_exp + en.exp_cf;
+  a.tab.Cb = (const Real *)en.d_exp + en.exp_cb;
+  a.seg = w.seg;
+  a.atom_of_pos = c->ov_atom_of_pos ? c->ov_atom_of_pos : w.atom_of_pos;
+  a.rows = rows;
+  a.xw = w.xw;
+  for (int k = 0; k < 3; ++k) a.L[k] = c->box_L[k];
+  a.nlist = w.nlist;
+  a.nreal = w.nreal;
+  a.flags = &w.status->flags;
+  a.mask = w.exp_mask;
+  a.H = a.M = (Real *)w.exp_hm;
+  if (prec16(c->precision)) {
+    a.T = (Real *)w.T32;
+    a.dT = (const Real *)w.dT32;
+  } else {
+    a.T = (Real *)w.T;
+    a.D = (Real *)w.D;
+    a.dD = (const Real *)w.dD;
+  }
+  a.force = F;
+  a.vir_part = w.vir_part;
+  a.net_deriv = c->keep ? w.net_deriv : nullptr;
+  return a;
+}
+
 // Formatted neighbour list and environment matrix of the current frame.
 void eval_lists(dp_ctx *c, int64_t n, const double L[3]) {
   Workspace &w = c->ws;
@@ -898,12 +1027,14 @@ void eval_lists(dp_ctx *c, int64_t n, const double L[3]) {
   // the mixed path's FP32 environment rows come out of the format kernel
   // (it has each slot's neighbour and position at hand); the FP64 path's
   // rows and displacements from the environment kernel
-  const bool fused = w.rt32 && !w.dr;
+  // (the expansion path forms them in its pair kernels)
+  const bool exp = use_exp(c);
+  const bool fused = !exp && w.rt32 && !w.dr;
   tmark(c, 1);
   launch_format(s, n, w.xw, d, L, w.cand, w.cand_n, w.cand_cap, w.nlist, w.nreal, &w.status->overflow,
                 w.status->max_real, &w.status->flags, fused ? w.rt32 : nullptr);
   tmark(c, 2);
-  if (!fused) launch_env(s, n, w.xw, d, L, w.nlist, w.nreal, w.rt, w.rt32, w.dr);
+  if (!fused && !exp) launch_env(s, n, w.xw, d, L, w.nlist, w.nreal, w.rt, w.rt32, w.dr);
   tmark(c, 3);
 }
 
@@ -1048,7 +1179,16 @@ void eval_nets_fwd(dp_ctx *c, int64_t n, double *E) {
   Workspace &w = c->ws;
   hipStream_t s = c->stream;
   const int64_t rows = eval_rows(c, n);
-  if (c->precision == DP_FP64) {
+  c->exp_now = use_exp(c);
+  if (c->exp_now) {
+    if (c->precision == DP_FP64) launch_exp_fwd<double>(s, exp_args<double>(c, rows, nullptr));
+    else launch_exp_fwd<float>(s, exp_args<float>(c, rows, nullptr));
+    tmark(c, 4);
+    if (c->precision == DP_FP64) launch_fit_f64(s, fit_args(c, rows), 1);
+    else if (c->precision == DP_MIX_FP32) launch_fit_f32(s, fit_args32(c, rows), 1);
+    else launch_fit_mix(s, fitmix_args(c, rows), 1);
+    tmark(c, 8);
+  } else if (c->precision == DP_FP64) {
     launch_embed_fwd_f64(s, embed_args(c, n, rows, nullptr));
     tmark(c, 4);
     launch_fit_f64(s, fit_args(c, rows), 1);
@@ -1121,7 +1261,20 @@ void eval_backward(dp_ctx *c, int64_t n, double *F, double *V) {
   Workspace &w = c->ws;
   hipStream_t s = c->stream;
   const int64_t rows = eval_rows(c, n);
-  if (!prec16(c->precision)) {
+  if (c->exp_now) {
+    if (c->precision == DP_FP64) launch_fit_f64(s, fit_args(c, rows), 2);
+    else if (c->precision == DP_MIX_FP32) launch_fit_f32(s, fit_args32(c, rows), 2);
+    else launch_fit_mix(s, fitmix_args(c, rows), 2);
+    tmark(c, 5);
+    launch_zero(s, F, 3 * (c->n_force > 0 ? c->n_force : n));
+    const int grid = exp_bwd_grid(rows);
+    tmark(c, 6);
+    if (c->precision == DP_FP64) launch_exp_bwd<double>(s, exp_args<double>(c, rows, F), grid);
+    else launch_exp_bwd<float>(s, exp_args<float>(c, rows, F), grid);
+    tmark(c, 9);
+    tmark(c, 7);
+    launch_sum9(s, w.vir_part, grid, V);
+  } else if (!prec16(c->precision)) {
     const bool f32 = c->precision == DP_MIX_FP32;
     if (f32) launch_fit_f32(s, fit_args32(c, rows), 2);
     else launch_fit_f64(s, fit_args(c, rows), 2);
@@ -1490,6 +1643,8 @@ int install_student(dp_ctx *c, HostModel &&m) {
     rc = upload_emb_mix(c, c->shm, c->en[1]);
     if (rc) return rc;
   }
+  rc = upload_exp(c, c->shm, c->en[1]);
+  if (rc) return rc;
   c->en[1].ready = true;
   return DP_OK;
 }
@@ -1605,6 +1760,7 @@ void dp_destroy(dp_ctx *c) {
     if (en.d_mix) (void)hipFree(en.d_mix);
     if (en.d_tab) (void)hipFree(en.d_tab);
     if (en.d_wide) (void)hipFree(en.d_wide);
+    if (en.d_exp) (void)hipFree(en.d_exp);
   }
   free_wide(c);
   free_student(c);
@@ -1644,6 +1800,8 @@ int dp_set_model(dp_ctx *c, const void *blob, size_t nbytes, int precision) {
     rc = upload_mix(c);
     if (rc) return rc;
   }
+  rc = upload_exp(c, c->hm, c->en[0]);
+  if (rc) return rc;
   c->has_model = true;
   return DP_OK;
 }
@@ -1664,7 +1822,11 @@ int dp_set_precision(dp_ctx *c, int precision) {
       return rc;
     }
   }
-  return DP_OK;
+  if (precision == old) return DP_OK;
+  c->en[0].exp_ok = c->en[1].exp_ok = false;  // the old precision's tables
+  int rc = upload_exp(c, c->hm, c->en[0]);
+  if (!rc && c->en[1].ready) rc = upload_exp(c, c->shm, c->en[1]);
+  return rc;
 }
 
 int dp_keep_intermediates(dp_ctx *c, int keep) {
@@ -1733,11 +1895,13 @@ static int compute_impl(dp_ctx *c, int64_t n, const double *coords, const int32_
   const int64_t ncell = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
   int cap = cand_capacity(n, L, rlist);
   c->fwd_ready = false;
+  c->exp_off = false;
   for (int attempt = 0; attempt < 4; ++attempt) {
     rc = ensure_ws(c, std::max<int64_t>(n, 1), ncell, cap);
     if (rc) return rc;
     Workspace &w = c->ws;
     double *F = forces ? forces : w.force_tmp;
+    const dp_stats before = c->stats;
     tmark(c, 0);
     hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, s, w.status, 0u);
     if (n > 0) {
@@ -1762,8 +1926,10 @@ static int compute_impl(dp_ctx *c, int64_t n, const double *coords, const int32_
     const uint32_t fl = c->h_status->flags;
     if (fl & FLAG_BAD_TYPE) return fail(c, DP_E_TYPE, "atom type out of range");
     if (fl & FLAG_KEY_CAP) return fail(c, DP_E_CAP, "more than 512 neighbours within rcut of one atom");
-    if (fl & FLAG_CAND_CAP) {
-      cap *= 2;
+    if (fl & (FLAG_CAND_CAP | FLAG_FAR)) {
+      if (fl & FLAG_CAND_CAP) cap *= 2;
+      else --attempt, c->stats = before;
+      if (fl & FLAG_FAR) c->exp_off = true;  // once more by the layers
       if (c->timing && c->nev > 0) --c->nev;
       continue;
     }
@@ -1812,11 +1978,13 @@ static int compute_local_impl(dp_ctx *c, int64_t n_local, int64_t n, const doubl
   int cap = cand_capacity(n, L, rlist);
   c->fwd_ready = false;
   c->last_n = 0;  // the lists below cover the centres only
+  c->exp_off = false;
   for (int attempt = 0; attempt < 4; ++attempt) {
     rc = ensure_ws(c, std::max<int64_t>(n, 1), ncell, cap);
     if (rc) return rc;
     Workspace &w = c->ws;
     double *F = forces ? forces : w.force_tmp;
+    const dp_stats before = c->stats;
     tmark(c, 0);
     hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, s, w.status, 0u);
     if (n_local > 0) {
@@ -1850,8 +2018,10 @@ static int compute_local_impl(dp_ctx *c, int64_t n_local, int64_t n, const doubl
     const uint32_t fl = c->h_status->flags;
     if (fl & FLAG_BAD_TYPE) return fail(c, DP_E_TYPE, "atom type out of range");
     if (fl & FLAG_KEY_CAP) return fail(c, DP_E_CAP, "more than 512 neighbours within rcut of one atom");
-    if (fl & FLAG_CAND_CAP) {
-      cap *= 2;
+    if (fl & (FLAG_CAND_CAP | FLAG_FAR)) {
+      if (fl & FLAG_CAND_CAP) cap *= 2;
+      else --attempt, c->stats = before;
+      if (fl & FLAG_FAR) c->exp_off = true;  // once more by the layers
       if (c->timing && c->nev > 0) --c->nev;
       continue;
     }
@@ -1901,7 +2071,7 @@ int dp_compute_noalloc(dp_ctx *c, int64_t n, const double *coords, const int32_t
   // The context's own workspace, and the state that describes its lists and
   // a pending dp_energy, are left as they are.
   const int64_t last_n = c->last_n;
-  const bool fwd_ready = c->fwd_ready, cgrid_ok = c->cgrid_ok;
+  const bool fwd_ready = c->fwd_ready, cgrid_ok = c->cgrid_ok, exp_now = c->exp_now;
   const CellGrid cgrid = c->cgrid;
   double box_L[3];
   std::memcpy(box_L, c->box_L, sizeof box_L);
@@ -1912,6 +2082,7 @@ int dp_compute_noalloc(dp_ctx *c, int64_t n, const double *coords, const int32_t
   std::swap(c->ws, c->ws_na);
   c->last_n = last_n;
   c->fwd_ready = fwd_ready;
+  c->exp_now = exp_now;
   c->cgrid_ok = cgrid_ok;
   c->cgrid = cgrid;
   std::memcpy(c->box_L, box_L, sizeof box_L);
@@ -2084,12 +2255,14 @@ int dp_md_run(dp_ctx *c, int64_t n, double *coords, double *vel, const int32_t *
     }
     return DP_OK;
   };
+  c->exp_off = false;
   rc = start(0);
   if (rc) return rc;
   int regrown = 0;
   // Read the flags after step st.  A skin-list overflow at a step after the
   // last check stopped the integrator there: the list is grown and the run
-  // restarted at that step (*resume); other errors end the run.
+  // restarted at that step (*resume), and so is a run that met a pair beyond
+  // the expansions, on the layers; other errors end the run.
   auto check = [&](int64_t st, int64_t &resume) -> int {
     HIPCHK(c, hipGetLastError());
     int r = read_status(c);
@@ -2097,14 +2270,20 @@ int dp_md_run(dp_ctx *c, int64_t n, double *coords, double *vel, const int32_t *
     const uint32_t fl = c->h_status->flags;
     if (fl & FLAG_BAD_TYPE) return fail(c, DP_E_TYPE, "atom type out of range");
     if (fl & FLAG_KEY_CAP) return fail(c, DP_E_CAP, "more than 512 neighbours within rcut of one atom");
-    if (fl & FLAG_NONFINITE) return fail(c, DP_E_NONFINITE, "non-finite energy by step " + std::to_string(st));
-    if (fl & FLAG_CAND_CAP) {
+    if ((fl & FLAG_NONFINITE) && !(fl & FLAG_FAR))
+      return fail(c, DP_E_NONFINITE, "non-finite energy by step " + std::to_string(st));
+    if (fl & (FLAG_CAND_CAP | FLAG_FAR)) {
       const long long f0 = nsteps == 0 ? 0 : c->h_status->fault_step;
-      if (regrown >= 4 || f0 < 0 || f0 > st)
+      if (((fl & FLAG_CAND_CAP) && regrown >= 4) || f0 < 0 || f0 > st)
         return fail(c, DP_E_CAP, "skin candidate list overflow; use a smaller skin");
-      ++regrown;
-      r = ensure_ws(c, n, ncell, 2 * c->ws.cand_cap);
-      if (r) return r;
+      // a pair came closer than the expansions reach: the rest of the run
+      // evaluates the layers
+      if (fl & FLAG_FAR) c->exp_off = true;
+      if (fl & FLAG_CAND_CAP) {
+        ++regrown;
+        r = ensure_ws(c, n, ncell, 2 * c->ws.cand_cap);
+        if (r) return r;
+      }
       r = start((int64_t)f0);
       if (r) return r;
       resume = (int64_t)f0;

@@ -44,10 +44,10 @@ struct FitOffsets {
 
 // Error flags written by kernels, read back by the host.
 enum : uint32_t { FLAG_BAD_TYPE = 1u, FLAG_CAND_CAP = 2u, FLAG_KEY_CAP = 4u, FLAG_NONFINITE = 8u,
-                  FLAG_REBUILD = 16u };
+                  FLAG_REBUILD = 16u, FLAG_FAR = 32u };
 // Flags that stop an MD run: once one is set, the integrator kernels leave
 // coordinates and velocities as they are until the host reads the flags.
-constexpr uint32_t FLAG_HALT = FLAG_BAD_TYPE | FLAG_CAND_CAP | FLAG_KEY_CAP | FLAG_NONFINITE;
+constexpr uint32_t FLAG_HALT = FLAG_BAD_TYPE | FLAG_CAND_CAP | FLAG_KEY_CAP | FLAG_NONFINITE | FLAG_FAR;
 
 struct NlistBufs {
   const double *coords;  // caller coords [n][3]
