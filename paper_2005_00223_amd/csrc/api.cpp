@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "dp_expand.h"
+#include "dp_fit_fused.h"
 #include "dp_internal.h"
 #include "dp_mix.h"
 #include "dp_wide.h"
@@ -244,6 +245,10 @@ struct dp_ctx {
   FitOffsets fo{};
   double *d_fit = nullptr;
   float *d_fit32 = nullptr;         // fitting weights rounded to FP32 (DP_MIX_FP32)
+  // FP64 / FP32 fitting weights packed as MFMA operands, in the real type of
+  // the precision in use (fused kernels)
+  void *d_fit_pack = nullptr;
+  FitPack fpk{};
   // mixed-precision fitting weights (16-bit MFMA operands + f32)
   unsigned char *d_fit_mix = nullptr;
   FitMixOffsets fmo{};
@@ -287,6 +292,7 @@ struct dp_ctx {
   } wb;
   int pending_rc = DP_OK;  // an error inside an evaluation (reported by read_status)
   bool exp_off = false;    // this call's frames hold a pair beyond the expansions: evaluate the layers
+  bool d_of_T = false;     // the last forward kept T but no D
   bool exp_now = false;    // the last forward ran on the expansions (its backward does too)
   int wide_split = 1;      // wide nets: activations stored as hi + lo 16-bit halves (0: one 16-bit value)
   // no-allocation entry point: the device address of this GPU's static
@@ -724,6 +730,23 @@ int upload_mix(dp_ctx *c) {
   return DP_OK;
 }
 
+// Fitting weights of the fused FP64 / FP32 kernels (none: the layer GEMMs run).
+int upload_fit_pack(dp_ctx *c) {
+  if (c->d_fit_pack) (void)hipFree(c->d_fit_pack);
+  c->d_fit_pack = nullptr;
+  if (prec16(c->precision) || !fit_fused_supported(c->dims)) return DP_OK;
+  c->fpk = fit_pack_layout(c->dims);
+  if (c->precision == DP_FP64) {
+    HIPCHK(c, hipMalloc(&c->d_fit_pack, sizeof(double) * c->fpk.total));
+    launch_fit_pack<double>(c->stream, c->dims, c->fo, c->d_fit, c->fpk, (double *)c->d_fit_pack);
+  } else {
+    HIPCHK(c, hipMalloc(&c->d_fit_pack, sizeof(float) * c->fpk.total));
+    launch_fit_pack<float>(c->stream, c->dims, c->fo, c->d_fit32, c->fpk, (float *)c->d_fit_pack);
+  }
+  HIPCHK(c, hipGetLastError());
+  return DP_OK;
+}
+
 // Expansions of the nets of m (dp_expand.h) for the precision in use, with
 // the weights its layer kernels hold.  Nets without one leave exp_ok false.
 template <typename Real>
@@ -982,6 +1005,31 @@ int64_t eval_rows(const dp_ctx *c, int64_t n) {
 // Whether an evaluation of the active nets runs on their expansions.
 inline bool use_exp(const dp_ctx *c) { return c->en[c->active].exp_ok && !c->exp_off && c->ws.exp_hm; }
 
+// ... and its fitting net in the fused kernels (no D, dE/dT in place of dE/dD)
+inline bool use_fused(const dp_ctx *c) { return c->exp_now && c->d_fit_pack; }
+
+template <typename Real>
+FitFusedArgs<Real> fused_args(dp_ctx *c, int64_t rows) {
+  Workspace &w = c->ws;
+  FitFusedArgs<Real> a{};
+  a.d = c->dims;
+  a.fo = c->fo;
+  a.fwt = sizeof(Real) == 8 ? (const Real *)c->d_fit : (const Real *)c->d_fit32;
+  a.pk = c->fpk;
+  a.pack = (const Real *)c->d_fit_pack;
+  a.type_start = c->ov_type_start ? c->ov_type_start : w.type_start;
+  a.atom_of_pos = c->ov_atom_of_pos ? c->ov_atom_of_pos : w.atom_of_pos;
+  a.rows = rows;
+  for (int l = 1; l <= a.d.n_fit; ++l) {
+    a.maxw = std::max(a.maxw, a.d.fw[l]);
+    a.Tt[l] = (Real *)w.Tt[l];
+  }
+  a.T = (const Real *)w.T;
+  a.dT = (Real *)w.dD;
+  a.eatom = w.eatom;
+  return a;
+}
+
 template <typename Real>
 ExpArgs<Real> exp_args(dp_ctx *c, int64_t rows, double *F) {
   Workspace &w = c->ws;
@@ -1009,8 +1057,12 @@ ExpArgs<Real> exp_args(dp_ctx *c, int64_t rows, double *F) {
     a.dT = (const Real *)w.dT32;
   } else {
     a.T = (Real *)w.T;
-    a.D = (Real *)w.D;
-    a.dD = (const Real *)w.dD;
+    if (use_fused(c)) {
+      a.dT = (const Real *)w.dD;
+    } else {
+      a.D = (Real *)w.D;
+      a.dD = (const Real *)w.dD;
+    }
   }
   a.force = F;
   a.vir_part = w.vir_part;
@@ -1173,6 +1225,21 @@ int wide_forward(dp_ctx *c, int64_t n) {
   return DP_OK;
 }
 
+// Fitting net (pass 1 forward, 2 backward) of an evaluation on the expansions.
+void fit_exp(dp_ctx *c, int64_t n, int64_t rows, int pass) {
+  hipStream_t s = c->stream;
+  if (use_fused(c)) {
+    if (c->precision == DP_FP64) launch_fit_fused<double>(s, fused_args<double>(c, rows), n, pass);
+    else launch_fit_fused<float>(s, fused_args<float>(c, rows), n, pass);
+  } else if (c->precision == DP_FP64) {
+    launch_fit_f64(s, fit_args(c, rows), pass);
+  } else if (c->precision == DP_MIX_FP32) {
+    launch_fit_f32(s, fit_args32(c, rows), pass);
+  } else {
+    launch_fit_mix(s, fitmix_args(c, rows), pass);
+  }
+}
+
 // Networks of the forward half with the active embedding set: embedding +
 // descriptor, fitting net forward, energy into E.
 void eval_nets_fwd(dp_ctx *c, int64_t n, double *E) {
@@ -1180,13 +1247,12 @@ void eval_nets_fwd(dp_ctx *c, int64_t n, double *E) {
   hipStream_t s = c->stream;
   const int64_t rows = eval_rows(c, n);
   c->exp_now = use_exp(c);
+  c->d_of_T = use_fused(c);
   if (c->exp_now) {
     if (c->precision == DP_FP64) launch_exp_fwd<double>(s, exp_args<double>(c, rows, nullptr));
     else launch_exp_fwd<float>(s, exp_args<float>(c, rows, nullptr));
     tmark(c, 4);
-    if (c->precision == DP_FP64) launch_fit_f64(s, fit_args(c, rows), 1);
-    else if (c->precision == DP_MIX_FP32) launch_fit_f32(s, fit_args32(c, rows), 1);
-    else launch_fit_mix(s, fitmix_args(c, rows), 1);
+    fit_exp(c, n, rows, 1);
     tmark(c, 8);
   } else if (c->precision == DP_FP64) {
     launch_embed_fwd_f64(s, embed_args(c, n, rows, nullptr));
@@ -1262,9 +1328,7 @@ void eval_backward(dp_ctx *c, int64_t n, double *F, double *V) {
   hipStream_t s = c->stream;
   const int64_t rows = eval_rows(c, n);
   if (c->exp_now) {
-    if (c->precision == DP_FP64) launch_fit_f64(s, fit_args(c, rows), 2);
-    else if (c->precision == DP_MIX_FP32) launch_fit_f32(s, fit_args32(c, rows), 2);
-    else launch_fit_mix(s, fitmix_args(c, rows), 2);
+    fit_exp(c, n, rows, 2);
     tmark(c, 5);
     launch_zero(s, F, 3 * (c->n_force > 0 ? c->n_force : n));
     const int grid = exp_bwd_grid(rows);
@@ -1767,6 +1831,7 @@ void dp_destroy(dp_ctx *c) {
   if (c->d_fit) (void)hipFree(c->d_fit);
   if (c->d_fit32) (void)hipFree(c->d_fit32);
   if (c->d_fit_mix) (void)hipFree(c->d_fit_mix);
+  if (c->d_fit_pack) (void)hipFree(c->d_fit_pack);
   if (c->h_status) (void)hipHostFree(c->h_status);
   for (auto &e : c->ev)
     if (e) (void)hipEventDestroy(e);
@@ -1802,6 +1867,8 @@ int dp_set_model(dp_ctx *c, const void *blob, size_t nbytes, int precision) {
   }
   rc = upload_exp(c, c->hm, c->en[0]);
   if (rc) return rc;
+  rc = upload_fit_pack(c);
+  if (rc) return rc;
   c->has_model = true;
   return DP_OK;
 }
@@ -1825,6 +1892,7 @@ int dp_set_precision(dp_ctx *c, int precision) {
   if (precision == old) return DP_OK;
   c->en[0].exp_ok = c->en[1].exp_ok = false;  // the old precision's tables
   int rc = upload_exp(c, c->hm, c->en[0]);
+  if (!rc) rc = upload_fit_pack(c);
   if (!rc && c->en[1].ready) rc = upload_exp(c, c->shm, c->en[1]);
   return rc;
 }
@@ -2071,7 +2139,7 @@ int dp_compute_noalloc(dp_ctx *c, int64_t n, const double *coords, const int32_t
   // The context's own workspace, and the state that describes its lists and
   // a pending dp_energy, are left as they are.
   const int64_t last_n = c->last_n;
-  const bool fwd_ready = c->fwd_ready, cgrid_ok = c->cgrid_ok, exp_now = c->exp_now;
+  const bool fwd_ready = c->fwd_ready, cgrid_ok = c->cgrid_ok, exp_now = c->exp_now, d_of_T = c->d_of_T;
   const CellGrid cgrid = c->cgrid;
   double box_L[3];
   std::memcpy(box_L, c->box_L, sizeof box_L);
@@ -2083,6 +2151,7 @@ int dp_compute_noalloc(dp_ctx *c, int64_t n, const double *coords, const int32_t
   c->last_n = last_n;
   c->fwd_ready = fwd_ready;
   c->exp_now = exp_now;
+  c->d_of_T = d_of_T;
   c->cgrid_ok = cgrid_ok;
   c->cgrid = cgrid;
   std::memcpy(c->box_L, box_L, sizeof box_L);
@@ -2152,7 +2221,9 @@ int dp_get_intermediates(dp_ctx *c, double *atom_e, double *T, double *D, double
     HIPCHK(c, hipMemcpyAsync(pos.data(), c->ws.pos_of_atom, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     const size_t MM = (size_t)d.M1 * d.M2;
-    if (D)
+    if (D && c->d_of_T)
+      launch_form_d(s, n, d.M1, d.M2, c->ws.T, D);  // the fused kernels keep none
+    else if (D)
       for (int64_t i = 0; i < n; ++i)
         HIPCHK(c, hipMemcpyAsync(D + i * MM, c->ws.D + (size_t)pos[i] * MM, sizeof(double) * MM,
                                  hipMemcpyDeviceToDevice, s));
