@@ -8,8 +8,8 @@
 //                (N = 4 atoms x 4 components), and D = T T_<^T (FP64 / FP32)
 //   k_exp_adj    four atoms per wave: dE/dT from dE/dD (FP64 / FP32), then
 //                M = C dE/dT and M' = C' dE/dT on the matrix cores
-//   k_exp_force  per atom: dE/dR_j from M, M', the FP64 force pass, F_j by
-//                FP64 atomics, virial partial sums
+//   k_exp_force  per atom: dE/dR_j from M, M', the FP64 force pass, F_j
+//                merged in LDS and added by FP64 atomics, virial partial sums
 //
 // The list is sorted by distance, so the neighbours of one net come in
 // descending s and each piece's are one run of slots; an atom's runs
@@ -23,18 +23,27 @@
 // M (2 K operands a lane) stay in registers; with one lane per neighbour H
 // would take 4 K accumulators and a wave reduction four times as long.
 //
-// Measured, 32,000 copper atoms (5.7 million pairs), the layer kernels
-// before and these after: FP64 forward 5.30 ms, now 0.19 (k_exp_pair 0.10,
-// k_exp_desc 0.09, which writes the 0.41 GB of D at 4.4 TB/s), backward 8.05
-// ms, now 0.70 (k_exp_adj 0.36, k_exp_force 0.34); FP32 3.19 and 6.03 ms.
-// FP16, 62,565 centres: forward 2.18 ms, now 0.17, backward 3.53 ms, now
-// 0.67.  k_exp_force is bound by its FP64 atomics.
+// Measured, 32,000 copper atoms (5.8 million pairs), the layer kernels before
+// and these now: FP64 forward 5.30 ms -> 0.12 (k_exp_pair 0.09, k_exp_desc
+// 0.03), backward 8.05 ms -> 0.30 (k_exp_adj 0.04, k_exp_force 0.26); FP32
+// forward 3.19 ms -> 0.08, backward 6.03 ms -> 0.21.  FP16, 62,565 centres:
+// forward 2.18 ms -> 0.15, backward 3.53 ms -> 0.38.
+// The pair kernels wait on latency (atom -> list -> positions -> pieces -> M)
+// more than they compute: atom data come by scalar loads, pieces are found
+// once per neighbour from lanes, positions and M are loaded ahead
+// (k_exp_pair 96 -> 90 us FP64, 72 -> 57 FP32).
 #include "dp_expand.h"
 #include "dp_f64.h"
 
 namespace dpk {
 
 constexpr int EXP_WAVES = 4;
+constexpr int EXP_ROWS = 16;         // rows of a run in k_exp_force
+constexpr int EXP_HASH_LOG = 10, EXP_HASH = 1 << EXP_HASH_LOG, EXP_PROBES = 8;
+// rows from which k_exp_force merges in LDS: below, 16 rows a workgroup leave
+// CUs idle (whole evaluation with | without, FP32 copper: 864 atoms 324 | 322
+// us, 4,000 380 | 400, 6,912 469 | 508)
+constexpr int64_t EXP_MERGE = 4096;
 
 template <typename Real>
 struct ExpK;
@@ -79,17 +88,74 @@ __device__ inline PairGeo pair_geo(const double4 &pi, const double4 &pj, const d
   return g;
 }
 
-// piece of s: the last one whose lower end is <= s (lo[0] = 0); the whole
-// wave stops at the first piece above all of its s
+// The pieces of one net, piece q's ends and scale in lane q (P <= 32).
 template <typename Real>
-__device__ inline int piece_of(const Real *__restrict__ pc, int P, Real s) {
-  int p = 0;
-  for (int q = 1; q < P; ++q) {
-    const bool up = s >= pc[4 * q];
-    if (!__ballot(up)) break;
-    p += up ? 1 : 0;
+struct Pieces {
+  Real lo, mid, ih;
+  __device__ void load(const Real *__restrict__ pc, int P, int lane) {
+    const Real *q = pc + 4 * (lane < P ? lane : P - 1);
+    lo = q[0];
+    mid = q[1];
+    ih = q[2];
   }
-  return p;
+  __device__ static double from(double v, int q) {
+    const long long b = __double_as_longlong(v);
+    return __longlong_as_double((long long)(unsigned)__builtin_amdgcn_readlane((int)b, q) |
+                                (long long)__builtin_amdgcn_readlane((int)(b >> 32), q) << 32);
+  }
+  __device__ static float from(float v, int q) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), q));
+  }
+  // piece of s: the last one whose lower end is <= s (lo[0] = 0); the whole
+  // wave stops at the first piece above all of its s
+  __device__ int of(int P, Real s) const {
+    int p = 0;
+    for (int q = 1; q < P; ++q) {
+      const bool up = s >= from(lo, q);
+      if (!__ballot(up)) break;
+      p += up ? 1 : 0;
+    }
+    return p;
+  }
+};
+
+// One net's neighbours of an atom, 64 at a time: positions are loaded one
+// block ahead, list entries two, so that neither latency stands between two
+// blocks.  Slots past the end reread the last one.
+struct PairStream {
+  const int32_t *list;
+  const double4 *xw;
+  int cnt, j, jn;
+  double4 x, xn;
+  __device__ int slot(int q) const { return list[q < cnt ? q : cnt - 1]; }
+  __device__ void begin(const int32_t *l, const double4 *p, int n, int lane) {
+    list = l;
+    xw = p;
+    cnt = n;
+    jn = slot(lane);
+    xn = xw[jn];
+    j = jn;
+    jn = slot(64 + lane);
+  }
+  // block at n0: j, x
+  __device__ void next(int n0, int lane) {
+    x = xn;
+    const int cur = j;
+    if (n0 + 64 < cnt) {
+      xn = xw[jn];
+      j = jn;
+      jn = slot(n0 + 128 + lane);
+    }
+    jcur = cur;
+  }
+  int jcur;
+};
+
+// workgroup barrier that orders LDS accesses only (atomics to memory stay in flight)
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ inline unsigned long long seg_bit(int P, int u, int p) { return 1ull << (u * P + (P - 1 - p)); }
@@ -136,14 +202,15 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_pair(ExpArgs<Real> a) {
   constexpr int K = ExpK<Real>::K;
   __shared__ Real Rs[EXP_WAVES][64 * 4];
   const Dims &d = a.d;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // uniform over the wave: the atom's data come by scalar loads
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t p = xcd_block(blockIdx.x, gridDim.x) * EXP_WAVES + wv;
   if (p >= a.rows) return;
-  const int i = a.atom_of_pos[p];
+  const int i = __builtin_amdgcn_readfirstlane(a.atom_of_pos[p]);
   if (i < 0) return;
   Real *Rw = Rs[wv];
   const double4 pi = a.xw[i];
-  const int t = (int)pi.w, P = a.tab.P, c = lane & 3;
+  const int t = __builtin_amdgcn_readfirstlane((int)pi.w), P = a.tab.P, c = lane & 3;
   const double inv_w = 1.0 / (d.rcut - d.rcut_smth);
   Real *Hi = a.H + (int64_t)i * a.seg * (EXP_KP * 4);
   unsigned long long mask = 0;
@@ -153,7 +220,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_pair(ExpArgs<Real> a) {
     const int cnt = a.nreal[(int64_t)i * d.ntypes + u];
     if (cnt == 0) continue;
     const int64_t base = (int64_t)i * d.nnei + d.off[u];
-    const Real *pc = a.tab.piece + (int64_t)(t * d.ntypes + u) * P * 4;
+    Pieces<Real> pc;
+    pc.load(a.tab.piece + (int64_t)(t * d.ntypes + u) * P * 4, P, lane);
+    PairStream ps;
+    ps.begin(a.nlist + base, a.xw, cnt, lane);
     Real acc[K];
     int cur = -1;
     Real mid = 0, ih = 0;
@@ -165,11 +235,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_pair(ExpArgs<Real> a) {
       ++slot;
     };
     for (int n0 = 0; n0 < cnt; n0 += 64) {
-      const int q = n0 + lane;
-      // slots past the block reread its last one and get a zero row
-      const int j = a.nlist[base + (q < cnt ? q : cnt - 1)];
-      const PairGeo g = pair_geo<sizeof(Real) == 8>(pi, a.xw[j], a.L, d.rcut_smth, inv_w);
-      const bool in = q < cnt;
+      ps.next(n0, lane);
+      const PairGeo g = pair_geo<sizeof(Real) == 8>(pi, ps.x, a.L, d.rcut_smth, inv_w);
+      const bool in = n0 + lane < cnt;  // slots past the end get a zero row
+      const int piece = pc.of(P, in ? (Real)g.R[0] : Real(0));
       far |= in && !((Real)g.R[0] <= a.tab.smax);
       wave_sync();
 #pragma unroll
@@ -180,7 +249,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_pair(ExpArgs<Real> a) {
         const int nl = sub * 16 + (lane >> 2);
         const Real s = Rw[nl * 4], Rc = Rw[nl * 4 + c];
         const bool valid = nl < left;
-        const int mine = piece_of(pc, P, s);
+        const int mine = __shfl(piece, nl);
         unsigned long long todo = __ballot(valid);
         while (todo) {
           // the next piece, in descending order; a neighbour whose s lies
@@ -189,8 +258,8 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_pair(ExpArgs<Real> a) {
           if (cur < 0 || np < cur) {
             if (cur >= 0) flush();
             cur = np;
-            mid = pc[4 * cur + 1];
-            ih = pc[4 * cur + 2];
+            mid = pc.from(pc.mid, cur);
+            ih = pc.from(pc.ih, cur);
 #pragma unroll
             for (int k = 0; k < K; ++k) acc[k] = 0;
           }
@@ -460,40 +529,71 @@ __global__ void __launch_bounds__(64) k_exp_adj(ExpArgs<Real> a) {
 // ---------------------------------------------------------------------------
 // forces and virial
 // ---------------------------------------------------------------------------
-template <typename Real>
-__global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_force(ExpArgs<Real> a) {
+// MERGE: 3 FP64 atomics a pair at memory reach 55 G/s whatever the rest of the
+// kernel does (32,000 copper atoms, 5.8 million pairs: 318 us in FP32, of
+// which 138 remain without them; a copy of F per XCD changed nothing, so it is
+// the atomic units, not the lines' movement).  A workgroup therefore takes 16
+// consecutive rows and adds its pairs' forces in an LDS table keyed by atom;
+// each atom's sum then goes to memory once.  Rows close in space share most
+// neighbours (ordered copper: 2,900 pairs, about 600 atoms).  A pair whose
+// places in the table are taken goes to memory by itself, so atoms in random
+// order, where nothing merges, cost what they did (1,441 against 1,439 us for
+// an FP32 evaluation).  318 -> 188 us FP32, 335 -> 258 FP64, 62,565 centres
+// 600 -> 339; 8 rows 204 us, 32 rows 224; a workgroup per cell of the cell
+// list with sums addressed by cell 208 to 380 (cells differ in size).
+template <typename Real, bool MERGE>
+__global__ void __launch_bounds__(64 * EXP_WAVES, sizeof(Real) == 8 ? 2 : 3) k_exp_force(ExpArgs<Real> a) {
   constexpr int K = ExpK<Real>::K;
   constexpr int MS = EXP_KP + 2;  // row stride of a component's coefficients in LDS
   __shared__ __align__(16) Real Rs[EXP_WAVES][64 * 4];
   __shared__ __align__(16) Real Ms[EXP_WAVES][8 * MS];
   __shared__ __align__(16) double Fs[EXP_WAVES][64 * 4];
   __shared__ double vred[EXP_WAVES][9];
+  __shared__ int32_t key[MERGE ? EXP_HASH : 1];       // atom of a sum, or -1
+  __shared__ double facc[MERGE ? 3 * EXP_HASH : 1];
+  __shared__ int turn;                                // next row of the workgroup's run
   const Dims &d = a.d;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 3;
+  // uniform over the wave: the atom's data come by scalar loads
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 3;
   Real *Rw = Rs[wv], *Mw = Ms[wv];
   double *Fw = Fs[wv];
   const int P = a.tab.P;
   const double inv_w = 1.0 / (d.rcut - d.rcut_smth);
-  const int64_t nwaves = (int64_t)gridDim.x * EXP_WAVES;
-  const int64_t gw = xcd_block(blockIdx.x, gridDim.x) * EXP_WAVES + wv;
-  const int64_t chunk = (a.rows + nwaves - 1) / nwaves;
-  const int64_t p_end = (gw + 1) * chunk < a.rows ? (gw + 1) * chunk : a.rows;
   double vir[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) vir[k] = 0.0;
-  for (int64_t p = gw * chunk; p < p_end; ++p) {
-    const int i = a.atom_of_pos[p];
-    if (i < 0) continue;
+  // where atom j's force sum is in LDS: linear probing, -1 when the places
+  // tried are all taken
+  auto slot_of = [&](int j) {
+    unsigned h = (unsigned)j * 2654435769u >> (32 - EXP_HASH_LOG);
+    for (int q = 0; q < EXP_PROBES; ++q) {
+      int k = key[h];
+      if (k == -1) k = atomicCAS(&key[h], -1, j);
+      if (k == -1 || k == j) return (int)h;
+      h = (h + 1) & (EXP_HASH - 1);
+    }
+    return -1;
+  };
+  auto add = [&](int j, int sl, int k, double v) {
+    if (MERGE && sl >= 0) atomicAdd(&facc[3 * sl + k], v);
+    else unsafeAtomicAdd(a.force + 3 * (int64_t)j + k, v);
+  };
+  auto atom = [&](int i) {
     const double4 pi = a.xw[i];
-    const int t = (int)pi.w;
-    const Real *Mi = a.M + (int64_t)i * a.seg * (2 * EXP_KP * 4);
+    const int t = __builtin_amdgcn_readfirstlane((int)pi.w);
+    // the segments' M and M' in order, each loaded when the one before is taken
+    const Real *Mi = a.M + (int64_t)i * a.seg * (2 * EXP_KP * 4) + lane;
+    Real va = Mi[0], vb = Mi[EXP_KP * 4];
     double fx = 0.0, fy = 0.0, fz = 0.0;
-    int slot = -1;
+    int slot = 0;
     for (int u = 0; u < d.ntypes; ++u) {
       const int cnt = a.nreal[(int64_t)i * d.ntypes + u];
       if (cnt == 0) continue;
       const int64_t base = (int64_t)i * d.nnei + d.off[u];
-      const Real *pc = a.tab.piece + (int64_t)(t * d.ntypes + u) * P * 4;
+      Pieces<Real> pc;
+      pc.load(a.tab.piece + (int64_t)(t * d.ntypes + u) * P * 4, P, lane);
+      PairStream ps;
+      ps.begin(a.nlist + base, a.xw, cnt, lane);
       int cur = -1;
       Real mid = 0, ih = 0, m0[K], m1[K];
 #pragma unroll
@@ -501,8 +601,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_force(ExpArgs<Real> a) {
       for (int n0 = 0; n0 < cnt; n0 += 64) {
         const int q = n0 + lane;
         const bool in = q < cnt;
-        const int j = a.nlist[base + (in ? q : cnt - 1)];
-        const PairGeo g = pair_geo<sizeof(Real) == 8>(pi, a.xw[j], a.L, d.rcut_smth, inv_w);
+        ps.next(n0, lane);
+        const int j = ps.jcur, jsl = MERGE && in ? slot_of(j) : -1;
+        const PairGeo g = pair_geo<sizeof(Real) == 8>(pi, ps.x, a.L, d.rcut_smth, inv_w);
+        const int piece = pc.of(P, in ? (Real)g.R[0] : Real(0));
         wave_sync();
 #pragma unroll
         for (int k = 0; k < 4; ++k) Rw[lane * 4 + k] = in ? (Real)g.R[k] : Real(0);
@@ -512,23 +614,22 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_force(ExpArgs<Real> a) {
           const int nl = sub * 16 + (lane >> 2);
           const Real s = Rw[nl * 4], Rc = Rw[nl * 4 + c];
           const bool valid = nl < left;
-          const int mine = piece_of(pc, P, s);
+          const int mine = __shfl(piece, nl);
           Real ga = 0, gb = 0;
           unsigned long long todo = __ballot(valid);
           while (todo) {
             const int np = __builtin_amdgcn_readlane(mine, __ffsll(todo) - 1);
             if (cur < 0 || np < cur) {
               cur = np;
-              ++slot;
-              mid = pc[4 * cur + 1];
-              ih = pc[4 * cur + 2];
-              // the segment's M and M', [k][component] in memory, to one
-              // component's coefficients per lane
-              const Real *Ml = Mi + (int64_t)(slot < a.seg ? slot : 0) * (2 * EXP_KP * 4);
-              const Real va = Ml[lane], vb = Ml[EXP_KP * 4 + lane];
+              mid = pc.from(pc.mid, cur);
+              ih = pc.from(pc.ih, cur);
+              // [k][component] in memory, to one component's coefficients per lane
               wave_sync();
               Mw[c * MS + (lane >> 2)] = va;
               Mw[(4 + c) * MS + (lane >> 2)] = vb;
+              slot += slot + 1 < a.seg ? 1 : 0;
+              va = Mi[slot * (2 * EXP_KP * 4)];
+              vb = Mi[slot * (2 * EXP_KP * 4) + EXP_KP * 4];
               wave_sync();
 #pragma unroll
               for (int k = 0; k < K; ++k) {
@@ -598,12 +699,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_force(ExpArgs<Real> a) {
         wave_sync();
         // F_j, a neighbour's three components from adjacent lanes: one
         // instruction's atomics then meet 16 cache lines instead of 64
-        // (62,565 centres: 1.17 -> 0.63 ms for the kernel against one lane
-        // per neighbour with three atomics each)
         for (int sub = 0; sub < 4 && sub * 16 < left; ++sub) {
           const int nl = sub * 16 + (lane >> 2);
-          const int jn = __shfl(j, nl);
-          if (c < 3 && nl < left) unsafeAtomicAdd(a.force + 3 * (int64_t)jn + c, Fw[nl * 4 + c]);
+          const int jn = __shfl(j, nl), sl = MERGE ? __shfl(jsl, nl) : -1;
+          if (c < 3 && nl < left) add(jn, sl, c, Fw[nl * 4 + c]);
         }
       }
     }
@@ -614,9 +713,52 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_force(ExpArgs<Real> a) {
       fz += __shfl_xor(fz, o);
     }
     if (lane == 0) {
-      unsafeAtomicAdd(a.force + 3 * (int64_t)i + 0, fx);
-      unsafeAtomicAdd(a.force + 3 * (int64_t)i + 1, fy);
-      unsafeAtomicAdd(a.force + 3 * (int64_t)i + 2, fz);
+      const int sl = MERGE ? slot_of(i) : -1;
+      add(i, sl, 0, fx);
+      add(i, sl, 1, fy);
+      add(i, sl, 2, fz);
+    }
+  };
+  if constexpr (MERGE) {
+    for (int o = threadIdx.x; o < EXP_HASH; o += 64 * EXP_WAVES) key[o] = -1;
+    for (int o = threadIdx.x; o < 3 * EXP_HASH; o += 64 * EXP_WAVES) facc[o] = 0.0;
+    // runs of EXP_ROWS rows (the rows are padded to a multiple), a contiguous
+    // range of them per workgroup
+    const int64_t runs = a.rows / EXP_ROWS, per = (runs + gridDim.x - 1) / gridDim.x;
+    const int64_t b0 = xcd_block(blockIdx.x, gridDim.x) * per;
+    for (int64_t b = b0; b < b0 + per && b < runs; ++b) {
+      if (threadIdx.x == 0) turn = EXP_WAVES;
+      lds_barrier();
+      for (int k = wv; k < EXP_ROWS;) {
+        const int i = __builtin_amdgcn_readfirstlane(a.atom_of_pos[b * EXP_ROWS + k]);
+        if (i >= 0) atom(i);
+        int nx = 0;
+        if (lane == 0) nx = atomicAdd(&turn, 1);
+        k = __builtin_amdgcn_readfirstlane(nx);
+      }
+      lds_barrier();
+      // the sums to memory, the table empty again
+      for (int o = threadIdx.x; o < 4 * EXP_HASH; o += 64 * EXP_WAVES) {
+        const int j = key[o >> 2];
+        if (j >= 0) {
+          if (c < 3) {
+            unsafeAtomicAdd(a.force + 3 * (int64_t)j + c, facc[3 * (o >> 2) + c]);
+            facc[3 * (o >> 2) + c] = 0.0;
+          } else {
+            key[o >> 2] = -1;
+          }
+        }
+      }
+    }
+    lds_barrier();
+  } else {
+    const int64_t nwaves = (int64_t)gridDim.x * EXP_WAVES;
+    const int64_t gw = xcd_block(blockIdx.x, gridDim.x) * EXP_WAVES + wv;
+    const int64_t chunk = (a.rows + nwaves - 1) / nwaves;
+    const int64_t p_end = (gw + 1) * chunk < a.rows ? (gw + 1) * chunk : a.rows;
+    for (int64_t p = gw * chunk; p < p_end; ++p) {
+      const int i = a.atom_of_pos[p];
+      if (i >= 0) atom(i);
     }
   }
 #pragma unroll
@@ -634,11 +776,10 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_force(ExpArgs<Real> a) {
   }
 }
 
-// workgroups of k_exp_force, a multiple of eight (contiguous runs per XCD)
 int exp_bwd_grid(int64_t rows) {
-  int64_t g = (rows + EXP_WAVES - 1) / EXP_WAVES;
+  int64_t g = rows >= EXP_MERGE ? rows / EXP_ROWS : (rows + EXP_WAVES - 1) / EXP_WAVES;
   g = (g + 7) / 8 * 8;
-  return (int)(g < 8 ? 8 : g > 2048 ? 2048 : g);
+  return (int)(g < 8 ? 8 : g > 2048 ? 2048 : g);  // a multiple of eight: contiguous runs per XCD
 }
 
 template <typename Real>
@@ -662,7 +803,10 @@ void launch_exp_bwd(hipStream_t s, const ExpArgs<Real> &a, int grid) {
     else
       hipLaunchKernelGGL((k_exp_adj<Real, false>), gq, dim3(64), 0, s, a);
   }
-  hipLaunchKernelGGL(k_exp_force<Real>, dim3(grid), dim3(64 * EXP_WAVES), 0, s, a);
+  if (a.rows >= EXP_MERGE)
+    hipLaunchKernelGGL((k_exp_force<Real, true>), dim3(grid), dim3(64 * EXP_WAVES), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_exp_force<Real, false>), dim3(grid), dim3(64 * EXP_WAVES), 0, s, a);
 }
 
 template void launch_exp_fwd<double>(hipStream_t, const ExpArgs<double> &);

@@ -160,3 +160,33 @@ def test_md_through_the_range():
     assert np.abs(xg.cpu().numpy() - xo).max() <= 1e-7
     assert np.abs(vg.cpu().numpy() - vo).max() <= 1e-7 * max(1.0, np.abs(vo).max())
     assert np.abs(th[:, 1:5] - tho[:, 1:5]).max() <= 1e-6 * np.abs(tho[:, 1:5]).max()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("order", ["lattice", "shuffled"])
+@pytest.mark.parametrize("reps", [(4, 2, 1), (4, 3, 1)])
+def test_merged_scatter(reps, order, prec):
+    """Forces merged in the workgroups' LDS tables (4,000 and 6,000 atoms, the
+    smallest that are): neighbours shared by consecutive rows, and rows in
+    random order, whose neighbours overflow the table.  The system is a cell
+    of 500 repeated, so every copy has the oracle's forces of the cell."""
+    from oracle import oracle as O
+    from paper_2005_00223_amd.model import DPModel
+    x, t, box = synth.fcc_copper(5, 3.634, 0.1, seed=4)
+    spec = synth.copper_model(1)
+    r = O.Oracle(synth.pack_blob(_held(spec, prec))).eval(x, t, box)
+    copies = np.stack(np.meshgrid(*[np.arange(k) for k in reps], indexing="ij"), -1).reshape(-1, 3)
+    X = (x[None] + copies[:, None] * box).reshape(-1, 3)
+    n = len(X)
+    p = np.random.default_rng(1).permutation(n) if order == "shuffled" else np.arange(n)
+    say(f"[expand] merged scatter {n} {order} {prec}")
+    m = DPModel(synth.pack_blob(spec), prec)
+    e, f, v = m.compute(X[p], np.tile(t, len(copies))[p], box * np.array(reps))
+    want = np.tile(r["force"], (len(copies), 1))[p]
+    fmax, vmax = max(1.0, np.abs(want).max()), max(1.0, np.abs(r["virial"]).max())
+    df = np.abs(f.cpu().numpy() - want).max() / fmax
+    de = abs(float(e) / len(copies) - r["energy"]) / np.abs(r["atom_e"]).sum()
+    dv = np.abs(v.cpu().numpy() / len(copies) - r["virial"]).max() / vmax
+    say(f"  F {df:.2e}, E {de:.2e}, V {dv:.2e}")
+    bar = {"fp64": (1e-9, 1e-10, 1e-9), "fp32": (2.0 ** -12,) * 3}[prec]
+    assert df <= bar[0] and de <= bar[1] and dv <= bar[2]
