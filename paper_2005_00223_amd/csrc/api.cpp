@@ -1429,11 +1429,13 @@ void eval_judge(dp_ctx *c, int64_t n) {
 
 void build_lists(dp_ctx *c, int64_t n, const CellGrid &g, double rlist, const uint32_t *cond) {
   Workspace &w = c->ws;
-  launch_cells(c->stream, n, w.xw, g, w.cell_of, w.cell_start, w.cell_fill, w.cell_atoms, w.cell_code, w.scan_tmp,
-               cond);
+  // the cell-ordered positions borrow xref: under cond the caller copies the
+  // new reference positions there after the build, and no one else reads it
+  launch_cells(c->stream, n, w.xw, g, w.cell_of, w.cell_start, w.cell_fill, w.cell_atoms, w.cell_code,
+               (CellPos *)w.xref, w.scan_tmp, cond);
   c->cgrid = g;
   c->cgrid_ok = true;
-  launch_candidates(c->stream, n, w.xw, g, w.cell_start, w.cell_atoms, rlist, w.cand_cap, w.cand, w.cand_n,
+  launch_candidates(c->stream, n, w.xw, g, w.cell_start, (const CellPos *)w.xref, rlist, w.cand_cap, w.cand, w.cand_n,
                     &w.status->flags, cond);
 }
 
@@ -2061,11 +2063,11 @@ static int compute_local_impl(dp_ctx *c, int64_t n_local, int64_t n, const doubl
       launch_type_sort(s, n_local, w.xw, d.ntypes, w.blk_counts, w.type_count, w.type_start, w.pos_of_atom,
                        w.atom_of_pos, w.rows_cap);
       // the cell list holds every atom, candidate lists the centres
-      launch_cells(s, n, w.xw, g, w.cell_of, w.cell_start, w.cell_fill, w.cell_atoms, w.cell_code, w.scan_tmp,
-                   nullptr);
+      launch_cells(s, n, w.xw, g, w.cell_of, w.cell_start, w.cell_fill, w.cell_atoms, w.cell_code,
+                   (CellPos *)w.xref, w.scan_tmp, nullptr);
       c->cgrid = g;
       c->cgrid_ok = true;
-      launch_candidates(s, n_local, w.xw, g, w.cell_start, w.cell_atoms, rlist, w.cand_cap, w.cand, w.cand_n,
+      launch_candidates(s, n_local, w.xw, g, w.cell_start, (const CellPos *)w.xref, rlist, w.cand_cap, w.cand, w.cand_n,
                         &w.status->flags, nullptr);
       c->n_force = n;
       eval_forward(c, n_local, L);

@@ -66,6 +66,12 @@ struct NlistBufs {
   uint32_t *flags;       // [1]
 };
 
+// position (FP32) and index of an atom in cell order
+struct alignas(16) CellPos {
+  float x, y, z;
+  int32_t j;
+};
+
 struct CellGrid {
   int nc[3];
   double side[3];
@@ -82,11 +88,12 @@ void launch_type_sort(hipStream_t s, int64_t n, const double4 *xw, int ntypes, i
 // `cond` (may be NULL): when given, the kernels do nothing unless
 // (*cond & FLAG_REBUILD) -- the MD driver decides on the device.
 // cell_code (may be NULL): per-atom cell coordinates and index inside the cell
+// xs [n]: the atoms in cell order, for launch_candidates
 void launch_cells(hipStream_t s, int64_t n, const double4 *xw, const CellGrid &g, int32_t *cell_of,
                   int32_t *cell_start, int32_t *cell_fill, int32_t *cell_atoms, uint32_t *cell_code,
-                  int32_t *scan_tmp, const uint32_t *cond);
+                  CellPos *xs, int32_t *scan_tmp, const uint32_t *cond);
 void launch_candidates(hipStream_t s, int64_t n, const double4 *xw, const CellGrid &g, const int32_t *cell_start,
-                       const int32_t *cell_atoms, double rlist, int cand_cap, int32_t *cand, int32_t *cand_n,
+                       const CellPos *xs, double rlist, int cand_cap, int32_t *cand, int32_t *cand_n,
                        uint32_t *flags, const uint32_t *cond);
 void launch_fill_u32(hipStream_t s, uint32_t *p, int64_t n, uint32_t v);
 // rt32 (may be NULL): also write the mixed path's FP32 environment rows of
