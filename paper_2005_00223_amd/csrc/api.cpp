@@ -1236,7 +1236,7 @@ void fit_exp(dp_ctx *c, int64_t n, int64_t rows, int pass) {
   } else if (c->precision == DP_MIX_FP32) {
     launch_fit_f32(s, fit_args32(c, rows), pass);
   } else {
-    launch_fit_mix(s, fitmix_args(c, rows), pass);
+    launch_fit_mix(s, fitmix_args(c, rows), pass, true);
   }
 }
 
@@ -1276,7 +1276,7 @@ void eval_nets_fwd(dp_ctx *c, int64_t n, double *E) {
       launch_embed_mix(s, ma, 1, mix_grid(rows));
     }
     tmark(c, 4);
-    launch_fit_mix(s, fitmix_args(c, rows), 1);
+    launch_fit_mix(s, fitmix_args(c, rows), 1, false);
     tmark(c, 8);
   }
   launch_sum(s, w.eatom, n, w.partial, E, 1.0);
@@ -1352,7 +1352,7 @@ void eval_backward(dp_ctx *c, int64_t n, double *F, double *V) {
     tmark(c, 7);
     launch_sum9(s, w.vir_part, grid, V);
   } else {
-    launch_fit_mix(s, fitmix_args(c, rows), 2);
+    launch_fit_mix(s, fitmix_args(c, rows), 2, false);
     tmark(c, 5);
     launch_zero(s, F, 3 * (c->n_force > 0 ? c->n_force : n));
     tmark(c, 6);

@@ -5,6 +5,26 @@
 
 namespace dpk {
 
+template <typename Real>
+struct V4;
+template <>
+struct V4<double> {
+  typedef double t __attribute__((ext_vector_type(4)));
+};
+template <>
+struct V4<float> {
+  typedef float t __attribute__((ext_vector_type(4)));
+};
+
+// four sums over the four lane groups: group g ends with component g
+template <typename Real>
+__device__ inline Real group_columns(const typename V4<Real>::t &p, int g) {
+  const bool b1 = g & 2, b0 = g & 1;
+  const Real s0 = (b0 ? p[1] : p[0]) + __shfl_xor(b0 ? p[0] : p[1], 16);
+  const Real s1 = (b0 ? p[3] : p[2]) + __shfl_xor(b0 ? p[2] : p[3], 16);
+  return (b1 ? s1 : s0) + __shfl_xor(b1 ? s0 : s1, 32);
+}
+
 constexpr int FITX_TILES = 16;  // 16-column tiles of a hidden layer, at most
 
 // Element offsets of the weights packed as MFMA A operands, per type and

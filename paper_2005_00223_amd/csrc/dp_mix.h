@@ -196,7 +196,9 @@ bool fit_mix_supported(const Dims &d, const char **why);
 void fit_mix_pack(const Dims &d, int prec, int nsplit, const double *const *W, const double *const *b,
                   std::vector<unsigned char> &buf, FitMixOffsets &fo);
 size_t fit_mix_tbuf_floats(const Dims &d, int64_t rows);
-// pass 1: forward layers and E_i; pass 2: backward to dE/dT
-void launch_fit_mix(hipStream_t s, const FitMixArgs &a, int pass);
+// pass 1: forward layers and E_i; pass 2: backward to dE/dT.  split (FP16 weights
+// only): the kernels that split a layer's columns over waves where the system
+// is small
+void launch_fit_mix(hipStream_t s, const FitMixArgs &a, int pass, bool split);
 
 }  // namespace dpk

@@ -114,17 +114,6 @@ template void launch_fit_pack<double>(hipStream_t, const Dims &, const FitOffset
 template void launch_fit_pack<float>(hipStream_t, const Dims &, const FitOffsets &, const float *, const FitPack &,
                                      float *);
 
-template <typename Real>
-struct V4;
-template <>
-struct V4<double> {
-  typedef double t __attribute__((ext_vector_type(4)));
-};
-template <>
-struct V4<float> {
-  typedef float t __attribute__((ext_vector_type(4)));
-};
-
 // a lane's four k-steps of a packed block (64 lanes, 16 bytes of each at a time)
 __device__ inline V4<double>::t wblock(const double *b, int lane) {
   typedef double v2 __attribute__((ext_vector_type(2)));
@@ -132,15 +121,6 @@ __device__ inline V4<double>::t wblock(const double *b, int lane) {
   return V4<double>::t{lo[0], lo[1], hi[0], hi[1]};
 }
 __device__ inline V4<float>::t wblock(const float *b, int lane) { return *(const V4<float>::t *)(b + 4 * lane); }
-
-// four sums over the four lane groups: group g ends with component g
-template <typename Real>
-__device__ inline Real group_columns(const typename V4<Real>::t &p, int g) {
-  const bool b1 = g & 2, b0 = g & 1;
-  const Real s0 = (b1 ? p[2] : p[0]) + __shfl_xor(b1 ? p[0] : p[2], 32);
-  const Real s1 = (b1 ? p[3] : p[1]) + __shfl_xor(b1 ? p[1] : p[3], 32);
-  return (b0 ? s1 : s0) + __shfl_xor(b0 ? s0 : s1, 16);
-}
 
 // the block's type and first row (type blocks start at multiples of ROW_TILE)
 template <typename Real>

@@ -1,5 +1,5 @@
 // Mixed-precision fitting net (Fig. 1(d,g); Section V-B "Mixed-precision
-// computation"), fused per tile of 16 type-sorted rows (one wave):
+// computation"), fused over tiles of 16 type-sorted rows:
 //
 //   forward   D = T T_<^T is formed on the fly from T (M1 x 4 per atom) as
 //             the B operand of the first layer, so D never reaches HBM; the
@@ -30,6 +30,7 @@
 #include <cstring>
 #include <vector>
 
+#include "dp_fit_fused.h"
 #include "dp_mix.h"
 
 namespace dpk {
@@ -74,6 +75,27 @@ __device__ inline FSplit<0> fsplit<0>(const float (&x)[4], const float (&y)[4]) 
   FSplit<0> s;
   split8_f16(x, y, s.hi, s.lo);
   return s;
+}
+
+// The column-split kernels below and the backward that takes over from them in
+// large systems (SAME) form the same values with the same roundings, so that an
+// atom's results do not depend on the size of its system: multiply-adds are
+// written out, and a value is FP32 before its halves are taken (a product or
+// sum folded into the conversion is rounded once instead of twice).
+template <int P>
+__device__ inline FSplit<P> fsplit_same(const float (&x)[4], const float (&y)[4]) {
+  float u[4], v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    u[k] = x[k];
+    v[k] = y[k];
+    asm("" : "+v"(u[k]));
+    asm("" : "+v"(v[k]));
+  }
+  return fsplit<P>(u, v);
+}
+__device__ inline float dot4(const float4 &a, const float4 &b) {
+  return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)));
 }
 
 __device__ inline float ftanh(float x) {
@@ -164,7 +186,7 @@ __device__ inline void bwd_issue(const FitMixArgs &a, int t, int gc, unsigned ch
 // kk, x, y) on the fly; SPLIT adds the lo weights (three products).  Every
 // chunk prefetches the next one of the sequence (issue) and ends with the
 // block barrier.
-template <int P, int MT, bool SPLIT, class Issue, class BX>
+template <int P, int MT, bool SPLIT, bool SAME, class Issue, class BX>
 __device__ inline void hidden_layer(unsigned char (*stage)[STAGE_BYTES], int &gc, int nchunks, Issue issue, BX bx,
                                     v4f (&acc)[FIT_NT][MT], int lane) {
   typedef typename FT<P>::v8 V;
@@ -180,7 +202,7 @@ __device__ inline void hidden_layer(unsigned char (*stage)[STAGE_BYTES], int &gc
       for (int nt = 0; nt < FIT_NT; ++nt) {
         float x[4], y[4];
         bx(nt, kk, x, y);
-        B[nt] = fsplit<P>(x, y);
+        B[nt] = SAME ? fsplit_same<P>(x, y) : fsplit<P>(x, y);
       }
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
@@ -217,7 +239,6 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_fwd(FitMixArgs a) {
   const int t = rtype(a.type_start, ntypes, r0);
   const int M1 = a.d.M1, NL = a.d.n_fit, KS0 = M1 / 2;
   const int64_t tile0 = r0 / 16 + (int64_t)wv * NT;
-  const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
   // padding rows (ia < 0) read atom 0's T, scaled by 0 in Tb: every load is
   // unconditional, so none of them waits behind a branch (M1 >= 16)
   int ia[NT];
@@ -318,8 +339,8 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_fwd(FitMixArgs a) {
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) acc[nt][mt] = v4f{b.x, b.y, b.z, b.w};
     }
-    if (l >= a.nsplit) hidden_layer<P, MT, true>(stage, gc, nchunks, issue, bx, acc, lane);
-    else hidden_layer<P, MT, false>(stage, gc, nchunks, issue, bx, acc, lane);
+    if (l >= a.nsplit) hidden_layer<P, MT, true, false>(stage, gc, nchunks, issue, bx, acc, lane);
+    else hidden_layer<P, MT, false, false>(stage, gc, nchunks, issue, bx, acc, lane);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -349,7 +370,11 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_fwd(FitMixArgs a) {
   }
 }
 
-template <int P, int MT>
+// rows a of D whose products are summed in one go under SAME (k_fitc_bwd: by
+// one wave): whole chunks here, whole groups of four there, four runs
+__host__ __device__ inline int fit_run(int M1) { return 4 * F0_CA * ((M1 + 16 * F0_CA - 1) / (16 * F0_CA)); }
+
+template <int P, int MT, bool SAME>
 __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_bwd(FitMixArgs a) {
   typedef typename FT<P>::v8 V;
   constexpr int NT = FIT_NT, KSH = (MT + 1) / 2;
@@ -416,8 +441,8 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_bwd(FitMixArgs a) {
       }
       if (nt == NT - 1 && kk + 2 < KSH) tload(kk + 2, tp[kk & 1]);
     };
-    if (l >= a.nsplit) hidden_layer<P, MT, true>(stage, gc, nchunks, issue, bx, acc, lane);
-    else hidden_layer<P, MT, false>(stage, gc, nchunks, issue, bx, acc, lane);
+    if (l >= a.nsplit) hidden_layer<P, MT, true, SAME>(stage, gc, nchunks, issue, bx, acc, lane);
+    else hidden_layer<P, MT, false, SAME>(stage, gc, nchunks, issue, bx, acc, lane);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -446,15 +471,15 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_bwd(FitMixArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) y[v] = 0.f;
       }
-      Bz[nt][kk] = fsplit<P>(x, y);
+      Bz[nt][kk] = SAME ? fsplit_same<P>(x, y) : fsplit<P>(x, y);
     }
   // dD one row a of D (16 features b) at a time, contracted with T:
   //   dE/dT[a][c] = sum_b dD[a][b] T[b][c] + [a < M2] sum_a' dD[a'][a] T[a'][c]
-  const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
   const float4 *Ti[NT];
   float4 *dTi[NT];
   float4 Tq[NT][4], Ta[NT];
   float dT2[NT][4][4];
+  float dTs[NT][4][4];  // SAME: the runs before this one
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     Ti[nt] = (const float4 *)(a.T32 + (int64_t)(ia[nt] < 0 ? 0 : ia[nt]) * M1 * 4);
@@ -465,10 +490,27 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_bwd(FitMixArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) dT2[nt][r][c] = 0.f;
+      for (int c = 0; c < 4; ++c) dT2[nt][r][c] = dTs[nt][r][c] = 0.f;
   }
   const float s = a.inv_nc;
+  auto flush = [&]() {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          dTs[nt][r][c] += dT2[nt][r][c];
+          dT2[nt][r][c] = 0.f;
+        }
+  };
+  int left = fit_run(M1);
   for (int ch = 0; ch < n0c; ++ch, ++gc) {
+    if (SAME && left == 0) {
+      flush();
+      left = fit_run(M1);
+    }
+    left -= F0_CA;
     if (gc + 1 < nchunks) issue(gc + 1, stage[(gc + 1) & 1]);
     const unsigned char *buf = stage[gc & 1];
     for (int q = 0; q < F0_CA; ++q) {
@@ -493,10 +535,18 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_bwd(FitMixArgs a) {
         const float4 ta = Ta[nt];
         if (aa + 1 < M1) Ta[nt] = Ti[nt][aa + 1];
         float4 pc;
-        pc.x = c[0] * Tq[nt][0].x + c[1] * Tq[nt][1].x + c[2] * Tq[nt][2].x + c[3] * Tq[nt][3].x;
-        pc.y = c[0] * Tq[nt][0].y + c[1] * Tq[nt][1].y + c[2] * Tq[nt][2].y + c[3] * Tq[nt][3].y;
-        pc.z = c[0] * Tq[nt][0].z + c[1] * Tq[nt][1].z + c[2] * Tq[nt][2].z + c[3] * Tq[nt][3].z;
-        pc.w = c[0] * Tq[nt][0].w + c[1] * Tq[nt][1].w + c[2] * Tq[nt][2].w + c[3] * Tq[nt][3].w;
+        if constexpr (SAME) {
+          const float4 c4 = make_float4(c[0], c[1], c[2], c[3]);
+          pc.x = dot4(make_float4(Tq[nt][0].x, Tq[nt][1].x, Tq[nt][2].x, Tq[nt][3].x), c4);
+          pc.y = dot4(make_float4(Tq[nt][0].y, Tq[nt][1].y, Tq[nt][2].y, Tq[nt][3].y), c4);
+          pc.z = dot4(make_float4(Tq[nt][0].z, Tq[nt][1].z, Tq[nt][2].z, Tq[nt][3].z), c4);
+          pc.w = dot4(make_float4(Tq[nt][0].w, Tq[nt][1].w, Tq[nt][2].w, Tq[nt][3].w), c4);
+        } else {
+          pc.x = c[0] * Tq[nt][0].x + c[1] * Tq[nt][1].x + c[2] * Tq[nt][2].x + c[3] * Tq[nt][3].x;
+          pc.y = c[0] * Tq[nt][0].y + c[1] * Tq[nt][1].y + c[2] * Tq[nt][2].y + c[3] * Tq[nt][3].y;
+          pc.z = c[0] * Tq[nt][0].z + c[1] * Tq[nt][1].z + c[2] * Tq[nt][2].z + c[3] * Tq[nt][3].z;
+          pc.w = c[0] * Tq[nt][0].w + c[1] * Tq[nt][1].w + c[2] * Tq[nt][2].w + c[3] * Tq[nt][3].w;
+        }
         pc.x += __shfl_xor(pc.x, 16);
         pc.y += __shfl_xor(pc.y, 16);
         pc.z += __shfl_xor(pc.z, 16);
@@ -520,6 +570,7 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_bwd(FitMixArgs a) {
     }
     dma_wait_all();
   }
+  flush();
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     if (ia[nt] < 0) continue;
@@ -528,10 +579,403 @@ __global__ void __launch_bounds__(64 * FIT_WAVES, 1) k_fit_bwd(FitMixArgs a) {
       const int b = 4 * g + r;
       if (b < M1) {
         const float4 q = sh[wv][nt][n][b];
-        dTi[nt][b] = make_float4((q.x + dT2[nt][r][0]) * s, (q.y + dT2[nt][r][1]) * s, (q.z + dT2[nt][r][2]) * s,
-                                 (q.w + dT2[nt][r][3]) * s);
+        dTi[nt][b] = make_float4((q.x + dTs[nt][r][0]) * s, (q.y + dTs[nt][r][1]) * s, (q.z + dTs[nt][r][2]) * s,
+                                 (q.w + dTs[nt][r][3]) * s);
       }
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same networks with the columns of a layer split over the four waves of a
+// workgroup of 16 RT rows (wave w: output tiles 4 w .. 4 w + 3).  In small
+// systems, where 128 rows a workgroup leave most CUs idle and one wave carries
+// every product of its rows in turn, this is what bounds the time: 500 atoms
+// forward 70 -> 24 us, backward 86 -> 27.  At 500,000 atoms the forward runs at
+// the rate a large FP16 product reaches on this card (1.0 PFLOP/s).  The B
+// operands, hi and lo halves, are built once, by the wave that holds their
+// features (its tiles are exactly the features of k-steps 2 w and 2 w + 1),
+// and shared through LDS; the weights go from L2 straight to registers, each
+// read by one wave, S k-steps ahead.
+// ---------------------------------------------------------------------------
+constexpr int FC_W = 4, FC_CT = 4;  // waves, output tiles of each
+static_assert(FC_W * FC_CT >= FIT_MT && FC_W * 2 == FIT_KSH, "every tile and k-step has a wave");
+
+template <int RT>
+struct FcShape {
+  static constexpr int R = 16 * RT;
+  static constexpr int S = RT == 4 ? 2 : 4;       // k-steps of D per stage
+  static constexpr int U = S * RT / FC_W;         // (k-step, 16 rows) units a wave forms per stage
+  static constexpr int XB = FIT_KSH * RT * 2048;  // bytes of a layer's operands: [k-step][16 rows][hi, lo][lane]
+  static_assert(2 * S * RT * 2048 <= XB && S * RT % FC_W == 0, "two stages fit the layer's operands");
+};
+
+// one 1 KB operand block of the wave's lanes
+template <int P>
+__device__ inline typename FT<P>::v8 fc_block(const unsigned char *img, int64_t b, int lane) {
+  return *(const typename FT<P>::v8 *)(img + b * 1024 + 16 * lane);
+}
+
+// acc += A x over one k-step: X = its operands in LDS, w (and wl) the weights
+template <int P, int RT, bool SPLIT>
+__device__ inline void fc_step(const unsigned char *X, const typename FT<P>::v8 (&w)[FC_CT],
+                               const typename FT<P>::v8 (&wl)[FC_CT], int lane, v4f (&acc)[RT][FC_CT]) {
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const typename FT<P>::v8 hi = fc_block<P>(X, 2 * r, lane), lo = fc_block<P>(X, 2 * r + 1, lane);
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c) acc[r][c] = FT<P>::mma(w[c], hi, acc[r][c]);
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c) acc[r][c] = FT<P>::mma(w[c], lo, acc[r][c]);
+    if (SPLIT)
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c) acc[r][c] = FT<P>::mma(wl[c], hi, acc[r][c]);
+  }
+}
+
+template <int P, int RT, bool SPLIT>
+__device__ inline void fc_layer(const unsigned char *img, const unsigned char *img_lo, const unsigned char *X,
+                                const int (&ct)[FC_CT], int lane, v4f (&acc)[RT][FC_CT]) {
+  typedef typename FT<P>::v8 V;
+  constexpr int PD = FcShape<RT>::S;
+  V w[PD][FC_CT], wl[PD][FC_CT];
+  auto load = [&](int kk) {
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c) {
+      w[kk % PD][c] = fc_block<P>(img, kk * FIT_MT + ct[c], lane);
+      if (SPLIT) wl[kk % PD][c] = fc_block<P>(img_lo, kk * FIT_MT + ct[c], lane);
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < PD; ++k) load(k);
+#pragma unroll
+  for (int kk = 0; kk < FIT_KSH; ++kk) {
+    fc_step<P, RT, SPLIT>(X + kk * RT * 2048, w[kk % PD], wl[kk % PD], lane, acc);
+    if (kk + PD < FIT_KSH) load(kk + PD);
+  }
+}
+
+// the wave's features v as the operands of k-steps 2 w and 2 w + 1
+template <int P, int RT>
+__device__ inline void fc_put(unsigned char *X, const float (&v)[RT][FC_CT][4], int wv, int lane) {
+  typedef typename FT<P>::v8 V;
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const FSplit<P> s = fsplit_same<P>(v[r][2 * q], v[r][2 * q + 1]);
+      unsigned char *o = X + ((2 * wv + q) * RT + r) * 2048 + 16 * lane;
+      *(V *)o = s.hi;
+      *(V *)(o + 1024) = s.lo;
+    }
+}
+
+// the workgroup's type; false where it has no atoms (block-uniform)
+template <int RT>
+__device__ inline bool fc_block_type(const FitMixArgs &a, int64_t &r0, int &t) {
+  r0 = (int64_t)blockIdx.x * FcShape<RT>::R;
+  if (r0 >= a.type_start[a.d.ntypes] || a.atom_of_pos[r0] < 0) return false;
+  t = rtype(a.type_start, a.d.ntypes, r0);
+  return true;
+}
+
+template <int P, int RT>
+__global__ void __launch_bounds__(64 * FC_W, 2) k_fitc_fwd(FitMixArgs a) {
+  typedef FcShape<RT> S_;
+  typedef typename FT<P>::v8 V;
+  constexpr int S = S_::S, U = S_::U;
+  __shared__ __align__(16) unsigned char X[S_::XB];
+  __shared__ float es[FC_W][S_::R];
+  int64_t r0;
+  int t;
+  if (!fc_block_type<RT>(a, r0, t)) return;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4,
+            n = lane & 15;
+  const int M1 = a.d.M1, NL = a.d.n_fit, KS0 = M1 / 2;
+  const unsigned char *W = a.w;
+  int ct[FC_CT];
+#pragma unroll
+  for (int c = 0; c < FC_CT; ++c) ct[c] = FC_CT * wv + c < FIT_MT ? FC_CT * wv + c : FIT_MT - 1;
+  v4f acc[RT][FC_CT];
+  auto bias = [&](int l) {
+    const float *b0 = (const float *)(W + a.fo.bias[t][l]);
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c) {
+      const float4 b = *(const float4 *)(b0 + 16 * ct[c] + 4 * g);
+#pragma unroll
+      for (int r = 0; r < RT; ++r) acc[r][c] = v4f{b.x, b.y, b.z, b.w};
+    }
+  };
+  bias(0);
+  {
+    // the wave forms D of 16 rows (rg), U k-steps (from q0) of a stage
+    const int rg = wv % RT, q0 = wv / RT * U;
+    const int ia = a.atom_of_pos[r0 + 16 * rg + n];
+    const float4 *Ti = (const float4 *)(a.T32 + (int64_t)(ia < 0 ? 0 : ia) * M1 * 4);
+    const float live = ia >= 0 ? 1.f : 0.f;
+    float4 Tb[8], ta[U];
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+      const float4 q = Ti[8 * (g & 1) + v];
+      Tb[v] = make_float4(q.x * live, q.y * live, q.z * live, q.w * live);
+    }
+    auto tload = [&](int st) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int kk = S * st + q0 + u;
+        ta[u] = Ti[2 * (kk < KS0 ? kk : KS0 - 1) + (g >> 1)];
+      }
+    };
+    auto form = [&](unsigned char *buf) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float x[4], y[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          x[v] = dot4(ta[u], Tb[v]);
+          y[v] = dot4(ta[u], Tb[v + 4]);
+        }
+        const FSplit<P> s = fsplit_same<P>(x, y);
+        unsigned char *o = buf + ((q0 + u) * RT + rg) * 2048 + 16 * lane;
+        *(V *)o = s.hi;
+        *(V *)(o + 1024) = s.lo;
+      }
+    };
+    const unsigned char *img = W + a.fo.a0f[t];
+    V w[S][FC_CT];
+    auto load = [&](int kk, V(&q)[FC_CT]) {
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c) q[c] = fc_block<P>(img, (int64_t)(kk < KS0 ? kk : KS0 - 1) * FIT_MT + ct[c], lane);
+    };
+    tload(0);
+#pragma unroll
+    for (int q = 0; q < S; ++q) load(q, w[q]);
+    form(X);
+    tload(1);
+    __syncthreads();
+    const int nst = (KS0 + S - 1) / S;
+    for (int st = 0; st < nst; ++st) {
+      const unsigned char *buf = X + (st & 1) * (S * RT * 2048);
+      if (st + 1 < nst) form(X + ((st + 1) & 1) * (S * RT * 2048));
+      tload(st + 2);
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        if (S * st + q < KS0) fc_step<P, RT, false>(buf + q * RT * 2048, w[q], w[q], lane, acc);
+        load(S * (st + 1) + q, w[q]);
+      }
+      __syncthreads();
+    }
+  }
+  float Y[RT][FC_CT][4];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) Y[r][c][q] = 0.f;
+  for (int l = 0;; ++l) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c) {
+        const bool own = FC_CT * wv + c < FIT_MT;  // a tile past the last counts as zeros
+        float th[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          th[q] = ftanh(acc[r][c][q]);
+          Y[r][c][q] += own ? th[q] : 0.f;
+        }
+        if (own)
+          *(float4 *)(tile_t<FIT_MT>(a.tbuf, r0 / 16 + r, NL, l, ct[c]) + 4 * lane) =
+              make_float4(th[0], th[1], th[2], th[3]);
+      }
+    if (l + 1 == NL) break;
+    if (l > 0) __syncthreads();  // the layer's operands have been read
+    fc_put<P, RT>(X, Y, wv, lane);
+    bias(l + 1);
+    __syncthreads();
+    if (l + 1 >= a.nsplit) fc_layer<P, RT, true>(W + a.fo.ahf[t][l + 1], W + a.fo.ahf_lo[t][l + 1], X, ct, lane, acc);
+    else fc_layer<P, RT, false>(W + a.fo.ahf[t][l + 1], nullptr, X, ct, lane, acc);
+  }
+  const float *wo = (const float *)(W + a.fo.wout[t]);
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    float e = 0.f;
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c) {
+      const float4 w4 = *(const float4 *)(wo + 16 * ct[c] + 4 * g);
+      e += dot4(make_float4(Y[r][c][0], Y[r][c][1], Y[r][c][2], Y[r][c][3]), w4);
+    }
+    e += __shfl_xor(e, 16);
+    e += __shfl_xor(e, 32);
+    if (g == 0) es[wv][16 * r + n] = e;
+  }
+  __syncthreads();
+  for (int o = threadIdx.x; o < S_::R; o += 64 * FC_W) {
+    const int ia = a.atom_of_pos[r0 + o];
+    if (ia >= 0) a.eatom[ia] = (double)((es[0][o] + es[1][o]) + (es[2][o] + es[3][o])) + (double)wo[256];
+  }
+}
+
+template <int P>
+__global__ void __launch_bounds__(64 * FC_W, 2) k_fitc_bwd(FitMixArgs a) {
+  constexpr int RT = 1;  // 32 rows need more registers than two waves per SIMD have
+  typedef FcShape<RT> S_;
+  typedef typename FT<P>::v8 V;
+  constexpr int PD = S_::S;
+  __shared__ __align__(16) unsigned char X[S_::XB];
+  __shared__ float4 low[S_::R][16];    // sum over a of dD[a][b] T[a]
+  __shared__ float first[S_::R][16][4]; // sum over b of dD[a][b] T[b], a < 16
+  int64_t r0;
+  int t;
+  if (!fc_block_type<RT>(a, r0, t)) return;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4,
+            n = lane & 15;
+  const int M1 = a.d.M1, NL = a.d.n_fit;
+  const unsigned char *W = a.w;
+  int ct[FC_CT];
+#pragma unroll
+  for (int c = 0; c < FC_CT; ++c) ct[c] = FC_CT * wv + c < FIT_MT ? FC_CT * wv + c : FIT_MT - 1;
+  float dY[RT][FC_CT][4];
+  {
+    const float *wo = (const float *)(W + a.fo.wout[t]);
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c) {
+      const float4 w4 = *(const float4 *)(wo + 16 * ct[c] + 4 * g);
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        dY[r][c][0] = w4.x;
+        dY[r][c][1] = w4.y;
+        dY[r][c][2] = w4.z;
+        dY[r][c][3] = w4.w;
+      }
+    }
+  }
+  // dz_l = dY (1 - t_l^2) as operands; then dY_{l-1} = W_l dz_l + dY_l
+  for (int l = NL - 1; l >= 0; --l) {
+    float dz[RT][FC_CT][4];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c) {
+        const float4 th = *(const float4 *)(tile_t<FIT_MT>(a.tbuf, r0 / 16 + r, NL, l, ct[c]) + 4 * lane);
+        const float tv[4] = {th.x, th.y, th.z, th.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          dz[r][c][q] = FC_CT * wv + c < FIT_MT ? dY[r][c][q] * fmaf(-tv[q], tv[q], 1.f) : 0.f;
+      }
+    if (l < NL - 1) __syncthreads();  // the layer's operands have been read
+    fc_put<P, RT>(X, dz, wv, lane);
+    __syncthreads();
+    if (l == 0) break;
+    v4f acc[RT][FC_CT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c) acc[r][c] = v4f{0.f, 0.f, 0.f, 0.f};
+    if (l >= a.nsplit) fc_layer<P, RT, true>(W + a.fo.ahb[t][l], W + a.fo.ahb_lo[t][l], X, ct, lane, acc);
+    else fc_layer<P, RT, false>(W + a.fo.ahb[t][l], nullptr, X, ct, lane, acc);
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dY[r][c][q] += acc[r][c][q];
+  }
+  // dE/dD, four rows a of D at a time (a run of rows a wave), contracted at
+  // once with T
+  int ia[RT];
+  const float4 *Ti[RT];
+  float4 Tq[RT][4];
+  float dT2[RT][4][4];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    ia[r] = a.atom_of_pos[r0 + 16 * r + n];
+    Ti[r] = (const float4 *)(a.T32 + (int64_t)(ia[r] < 0 ? 0 : ia[r]) * M1 * 4);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      Tq[r][q] = Ti[r][4 * g + q];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) dT2[r][q][c] = 0.f;
+    }
+  }
+  const float s = a.inv_nc;
+  const unsigned char *img = W + a.fo.a0b[t];
+  auto load = [&](int grp, int kk, V(&q)[FC_CT]) {
+#pragma unroll
+    for (int c = 0; c < FC_CT; ++c) {
+      const int aa = FC_CT * grp + c;
+      q[c] = fc_block<P>(img, (int64_t)(aa < M1 ? aa : M1 - 1) * FIT_KSH + kk, lane);
+    }
+  };
+  const int G = fit_run(M1) / FC_CT;  // groups of rows of a wave
+  V w[PD][FC_CT];
+#pragma unroll
+  for (int k = 0; k < PD; ++k) load(G * wv, k, w[k]);
+  for (int grp = G * wv; grp < G * (wv + 1) && FC_CT * grp < M1; ++grp) {
+    v4f cc[RT][FC_CT];
+    float4 ta[RT][FC_CT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c) {
+        cc[r][c] = v4f{0.f, 0.f, 0.f, 0.f};
+        ta[r][c] = Ti[r][FC_CT * grp + c < M1 ? FC_CT * grp + c : M1 - 1];
+      }
+#pragma unroll
+    for (int kk = 0; kk < FIT_KSH; ++kk) {
+      fc_step<P, RT, false>(X + kk * RT * 2048, w[kk % PD], w[kk % PD], lane, cc);
+      load(kk + PD < FIT_KSH ? grp : grp + 1, (kk + PD) % FIT_KSH, w[kk % PD]);
+    }
+    // cc[r][c][q] = dE/dD[row n][a = 4 grp + c][b = 4 g + q]
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < FC_CT; ++c) {
+        const int aa = FC_CT * grp + c;
+        if (aa >= M1) continue;
+        const v4f z = cc[r][c];
+        const float4 z4 = make_float4(z[0], z[1], z[2], z[3]);
+        const float4 *T4 = Tq[r];
+        const v4f p = {dot4(make_float4(T4[0].x, T4[1].x, T4[2].x, T4[3].x), z4),
+                       dot4(make_float4(T4[0].y, T4[1].y, T4[2].y, T4[3].y), z4),
+                       dot4(make_float4(T4[0].z, T4[1].z, T4[2].z, T4[3].z), z4),
+                       dot4(make_float4(T4[0].w, T4[1].w, T4[2].w, T4[3].w), z4)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          dT2[r][q][0] = fmaf(z[q], ta[r][c].x, dT2[r][q][0]);
+          dT2[r][q][1] = fmaf(z[q], ta[r][c].y, dT2[r][q][1]);
+          dT2[r][q][2] = fmaf(z[q], ta[r][c].z, dT2[r][q][2]);
+          dT2[r][q][3] = fmaf(z[q], ta[r][c].w, dT2[r][q][3]);
+        }
+        const float v = group_columns<float>(p, g);
+        if (aa < 16) first[16 * r + n][aa][g] = v;
+        else if (ia[r] >= 0) a.dT32[((int64_t)ia[r] * M1 + aa) * 4 + g] = v * s;
+      }
+  }
+  // the sums over a of the waves, in order, onto the first 16 rows
+  for (int wi = 0; wi < FC_W; ++wi) {
+    if (wi == wv)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float4 o = wi ? low[16 * r + n][4 * g + q] : make_float4(0.f, 0.f, 0.f, 0.f);
+          o.x += dT2[r][q][0];
+          o.y += dT2[r][q][1];
+          o.z += dT2[r][q][2];
+          o.w += dT2[r][q][3];
+          low[16 * r + n][4 * g + q] = o;
+        }
+    __syncthreads();
+  }
+  for (int o = threadIdx.x; o < S_::R * 16; o += 64 * FC_W) {
+    const int i = a.atom_of_pos[r0 + (o >> 4)], b = o & 15;
+    if (i < 0) continue;
+    const float4 q = low[o >> 4][b];
+    const float *f = first[o >> 4][b];
+    *(float4 *)(a.dT32 + ((int64_t)i * M1 + b) * 4) =
+        make_float4((f[0] + q.x) * s, (f[1] + q.y) * s, (f[2] + q.z) * s, (f[3] + q.w) * s);
   }
 }
 
@@ -662,16 +1106,53 @@ size_t fit_mix_tbuf_floats(const Dims &d, int64_t rows) {
   return (size_t)((rows + 15) / 16) * d.n_fit * FIT_MT * 256;
 }
 
-void launch_fit_mix(hipStream_t s, const FitMixArgs &a, int pass) {
-  const unsigned grid = (unsigned)((a.rows + FIT_ROWS - 1) / FIT_ROWS);
-  if (grid == 0) return;
+// Time of a launch (us, 1600-240-240-240), from the rounds of workgroups that
+// 256 CUs need; the column split with the fewest rows a workgroup that still
+// fills them is the fastest, one with more reads fewer weights a row.
+// Measured:
+//   rows                     192  2,048  6,144  12,288  16,384  24,576  40,960  62,565
+//   forward 16 rows           24     25     38      57      73     103     166     270
+//           32                32     33     38      50      53      71     115     181
+//           64                50     51     56      64      66      82     135     166
+//   row-wave                  70     71     75      78      80      85     158     174
+//   backward 16 rows          26     28     48      68      89     141     229     439
+//           32                56     62     76     112     120     196     338     538, not built)
+//           row-wave          86     87     95      98     101     108     205     250
+static void launch_fit_split(hipStream_t s, const FitMixArgs &a, int pass) {
   if (pass == 1) {
-    if (a.prec == 0) hipLaunchKernelGGL((k_fit_fwd<0, FIT_MT>), dim3(grid), dim3(64 * FIT_WAVES), 0, s, a);
-    else hipLaunchKernelGGL((k_fit_fwd<1, FIT_MT>), dim3(grid), dim3(64 * FIT_WAVES), 0, s, a);
+    auto rounds = [&](int R) { return (a.rows + 256 * R - 1) / (256 * R); };
+    const double t1 = 13.0 + 15.0 * rounds(16), t2 = rounds(32) == 1 ? 36.0 : 22.5 * rounds(32),
+                 t4 = rounds(64) == 1 ? 60.0 : 42.0 * rounds(64);
+    auto go = [&](auto k, int R) {
+      hipLaunchKernelGGL(k, dim3((unsigned)(a.rows / R)), dim3(64 * FC_W), 0, s, a);
+    };
+    if (t1 <= t2 && t1 <= t4) go(k_fitc_fwd<0, 1>, 16);
+    else if (t2 <= t4) go(k_fitc_fwd<0, 2>, 32);
+    else go(k_fitc_fwd<0, 4>, 64);
+  } else if (a.rows <= 16384) {
+    hipLaunchKernelGGL((k_fitc_bwd<0>), dim3((unsigned)(a.rows / 16)), dim3(64 * FC_W), 0, s, a);
   } else {
-    if (a.prec == 0) hipLaunchKernelGGL((k_fit_bwd<0, FIT_MT>), dim3(grid), dim3(64 * FIT_WAVES), 0, s, a);
-    else hipLaunchKernelGGL((k_fit_bwd<1, FIT_MT>), dim3(grid), dim3(64 * FIT_WAVES), 0, s, a);
+    hipLaunchKernelGGL((k_fit_bwd<0, FIT_MT, true>), dim3((unsigned)(a.rows / FIT_ROWS)), dim3(64 * FIT_WAVES), 0, s,
+                       a);
   }
+}
+
+// The embedding layers' own kernels (BF16, student and wide nets) round what
+// they get from here to 16 bits, which turns a last bit of dE/dT into 1e-5 of a
+// force: behind them the row-wave kernels run at every size, one order of
+// summation for all.
+template <int P>
+static void launch_fit_rows(hipStream_t s, const FitMixArgs &a, int pass) {
+  const dim3 grid((unsigned)(a.rows / FIT_ROWS)), block(64 * FIT_WAVES);
+  if (pass == 1) hipLaunchKernelGGL((k_fit_fwd<P, FIT_MT>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_fit_bwd<P, FIT_MT, false>), grid, block, 0, s, a);
+}
+
+void launch_fit_mix(hipStream_t s, const FitMixArgs &a, int pass, bool split) {
+  if (a.rows <= 0) return;
+  if (split) launch_fit_split(s, a, pass);
+  else if (a.prec == 0) launch_fit_rows<0>(s, a, pass);
+  else launch_fit_rows<1>(s, a, pass);
 }
 
 }  // namespace dpk

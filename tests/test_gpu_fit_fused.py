@@ -86,3 +86,33 @@ def test_fit_fused(fit, M2, reps, prec):
     print(f"  F {df:.2e} of {fmax:.3g}, E {de:.2e}, V {dv:.2e} of {vmax:.3g}", flush=True)
     bar = {"fp64": (1e-9, 1e-10, 1e-9), "fp32": (2.0 ** -12,) * 3}[prec]
     assert df <= bar[0] and de <= bar[1] and dv <= bar[2]
+
+
+@pytest.mark.parametrize("prec", ["fp16"])
+@pytest.mark.parametrize("fit", [(240, 240, 240), (240,)])
+@pytest.mark.parametrize("reps", [(7, 7, 1), (16, 10, 1)])
+def test_fit_mix_sizes(reps, fit, prec):
+    """16-bit fitting net: 16 rows a workgroup (187 atoms, which the tests of
+    the precisions compare with the oracle) against 32 (9,163) and 64 forward
+    and the row-wave backward (29,920).  The products are the same in the same
+    order; the sums over tiles and rows of D are FP32 in another: 2^-16 of the
+    largest force and of the summed |E_i|."""
+    from paper_2005_00223_amd.model import DPModel
+    spec = synth.random_model(2, 4.5, 2.0, (64, 64), fit=fit, seed=21, out_scale=-8.0, desc_norm=2.0)
+    x, t, box = _cell()
+    m = DPModel(synth.pack_blob(spec), prec)
+    e1, f1, v1 = m.compute(x, t, box, keep_intermediates=True)
+    e1, f1, v1 = float(e1), f1.cpu().numpy(), v1.cpu().numpy()
+    scale = np.abs(m.intermediates(CELL, 100, 16, spec.nnei, ("atom_e",))["atom_e"].cpu().numpy()).sum()
+    copies = np.stack(np.meshgrid(*[np.arange(k) for k in reps], indexing="ij"), -1).reshape(-1, 3)
+    X = (x[None] + copies[:, None] * box).reshape(-1, 3)
+    perm = np.random.default_rng(2).permutation(len(X))
+    print(f"[fit] {fit} {prec}: {len(X)} atoms", flush=True)
+    sys.stdout.flush()
+    e, f, v = m.compute(X[perm], np.tile(t, len(copies))[perm], box * np.array(reps))
+    want = np.tile(f1, (len(copies), 1))[perm]
+    df = np.abs(f.cpu().numpy() - want).max() / np.abs(f1).max()
+    de = abs(float(e) / len(copies) - e1) / scale
+    dv = np.abs(v.cpu().numpy() / len(copies) - v1).max() / np.abs(v1).max()
+    print(f"  F {df:.2e}, E {de:.2e}, V {dv:.2e}", flush=True)
+    assert max(df, de, dv) <= 2.0 ** -16
