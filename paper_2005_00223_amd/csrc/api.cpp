@@ -1027,6 +1027,10 @@ FitFusedArgs<Real> fused_args(dp_ctx *c, int64_t rows) {
   a.T = (const Real *)w.T;
   a.dT = (Real *)w.dD;
   a.eatom = w.eatom;
+  if (a.d.fw[1] + 256 <= a.d.M1 * a.d.M2) {  // in the place of D, which this path does not form
+    a.gz = (Real *)w.D;
+    a.low = a.gz + rows * a.d.fw[1];
+  }
   return a;
 }
 

@@ -51,6 +51,9 @@ struct FitFusedArgs {
   Real *Tt[MAXF + 1];         // tanh outputs, per 16 rows [tile][lane][4]
   Real *dT;                   // [natoms][M1][4] dE/dT of the unscaled sum (pass 2)
   double *eatom;              // [natoms] (pass 1)
+  // small systems, or NULL: gz of layer 0 [rows][fw[1]] and the sums over rows
+  // of D [4][rows][16][4] on their way between the kernels of pass 2
+  Real *gz, *low;
 };
 
 // Whether the kernels take the model: M1 <= 128, hidden widths multiples of

@@ -45,6 +45,12 @@ constexpr int EXP_HASH_LOG = 10, EXP_HASH = 1 << EXP_HASH_LOG, EXP_PROBES = 8;
 // us, 4,000 380 | 400, 6,912 469 | 508)
 constexpr int64_t EXP_MERGE = 4096;
 
+// rows up to which four workgroups share the feature tiles (k_exp_desc) or the
+// segments (k_exp_adj) of four atoms: one wave per four atoms is a serial chain
+// of both on a mostly idle chip (192 water atoms FP64: 20.7 -> 6.8 us and 22.8
+// -> 11.0)
+constexpr int64_t EXP_SPREAD = 2048;
+
 template <typename Real>
 struct ExpK;
 template <>
@@ -289,9 +295,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES) k_exp_pair(ExpArgs<Real> a) {
 // ---------------------------------------------------------------------------
 // T = C^T H / Nc, D = T T_<^T
 // ---------------------------------------------------------------------------
-constexpr int EXP_MT = 8;  // feature tiles a wave accumulates at once
-
-template <typename Real, bool WITH_D>
+// EXP_MT: feature tiles a wave accumulates at once; without D the tiles may be
+// dealt to gridDim.y workgroups
+template <typename Real, bool WITH_D, int EXP_MT>
 __global__ void __launch_bounds__(64) k_exp_desc(ExpArgs<Real> a) {
   extern __shared__ __align__(16) unsigned char exp_smem[];
   Real *Ts = (Real *)exp_smem;  // WITH_D: [4][M1p][4]
@@ -322,7 +328,7 @@ __global__ void __launch_bounds__(64) k_exp_desc(ExpArgs<Real> a) {
     }
   }
   const Real *Hm = a.H + (int64_t)(im < 0 ? 0 : im) * a.seg * (EXP_KP * 4) + c;
-  for (int mt0 = 0; mt0 < nmt; mt0 += EXP_MT) {
+  for (int mt0 = blockIdx.y * EXP_MT; mt0 < nmt; mt0 += gridDim.y * EXP_MT) {
     typename MF<Real>::acc acc[EXP_MT];
 #pragma unroll
     for (int m = 0; m < EXP_MT; ++m) acc[m] = typename MF<Real>::acc{0, 0, 0, 0};
@@ -480,7 +486,9 @@ __global__ void __launch_bounds__(64) k_exp_adj(ExpArgs<Real> a) {
   }
   const Real *dTg = FROM_D ? dTs + (int64_t)r4 * M1p * 4 + c : a.dT + (int64_t)(im < 0 ? 0 : im) * M1 * 4 + c;
   const int mlast = FROM_D ? M1p - 1 : M1 - 1;
+  unsigned turn = 0;  // the segments are dealt to gridDim.y workgroups
   for (unsigned long long todo = any; todo; todo &= todo - 1) {
+    if (turn++ % gridDim.y != blockIdx.y) continue;
     const int b = __ffsll(todo) - 1;
     const int u = b / P, pc = P - 1 - b % P;
     const Real *C = a.tab.Cb + ((int64_t)(t * d.ntypes + u) * P + pc) * 2 * M1p * EXP_KP + col;
@@ -789,9 +797,11 @@ void launch_exp_fwd(hipStream_t s, const ExpArgs<Real> &a) {
   hipLaunchKernelGGL(k_exp_pair<Real>, dim3((unsigned)nb), dim3(64 * EXP_WAVES), 0, s, a);
   const dim3 gq((unsigned)(a.rows / 4));
   if (a.D)
-    hipLaunchKernelGGL((k_exp_desc<Real, true>), gq, dim3(64), sizeof(Real) * 16 * a.tab.M1p, s, a);
+    hipLaunchKernelGGL((k_exp_desc<Real, true, 8>), gq, dim3(64), sizeof(Real) * 16 * a.tab.M1p, s, a);
+  else if (a.rows <= EXP_SPREAD)
+    hipLaunchKernelGGL((k_exp_desc<Real, false, 2>), dim3(gq.x, 4), dim3(64), 0, s, a);
   else
-    hipLaunchKernelGGL((k_exp_desc<Real, false>), gq, dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_exp_desc<Real, false, 8>), gq, dim3(64), 0, s, a);
 }
 
 template <typename Real>
@@ -801,7 +811,7 @@ void launch_exp_bwd(hipStream_t s, const ExpArgs<Real> &a, int grid) {
     if (a.dD)
       hipLaunchKernelGGL((k_exp_adj<Real, true>), gq, dim3(64), sizeof(Real) * 16 * a.tab.M1p, s, a);
     else
-      hipLaunchKernelGGL((k_exp_adj<Real, false>), gq, dim3(64), 0, s, a);
+      hipLaunchKernelGGL((k_exp_adj<Real, false>), dim3(gq.x, a.rows <= EXP_SPREAD ? 4 : 1), dim3(64), 0, s, a);
   }
   if (a.rows >= EXP_MERGE)
     hipLaunchKernelGGL((k_exp_force<Real, true>), dim3(grid), dim3(64 * EXP_WAVES), 0, s, a);

@@ -182,10 +182,10 @@ __device__ inline void fitx_layer(const Real *__restrict__ W, int nk, int nt, co
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <typename Real, int RT>
+template <typename Real, int RT, int W>
 struct FwdShape {
   static constexpr int R = 16 * RT;
-  static constexpr int AG = 64 * NW / (4 * R);            // rows of D formed at a time
+  static constexpr int AG = 64 * W / (4 * R);             // rows of D formed at a time
   static constexpr int AS = AG < FX_PD ? FX_PD : AG;      // rows of D per stage
   static constexpr int DS = 16 * AS + 1;                  // row stride of the staged D
   static size_t lds(int maxw) {
@@ -194,13 +194,94 @@ struct FwdShape {
   }
 };
 
-template <typename Real, int RT>
-__global__ void __launch_bounds__(64 * NW, 1) k_fitx_fwd(FitFusedArgs<Real> a) {
-  typedef FwdShape<Real, RT> S;
+// layer 0 of the workgroup's rows for the wave's C column tiles: K = (a, b), D
+// formed by the W waves in LDS stages of AS rows a (at X)
+template <typename Real, int RT, int W, int C>
+__device__ inline void fitx_first(const FitFusedArgs<Real> &a, int t, int64_t r0, int64_t r1, const int (&ct)[C], Real *X,
+                                  int tid, typename MF<Real>::acc (&acc)[RT][C]) {
+  typedef FwdShape<Real, RT, W> S;
   typedef typename MF<Real>::acc acc_t;
   typedef typename V4<Real>::t v4;
   constexpr int R = S::R, AS = S::AS, DS = S::DS;
   static_assert(AS % S::AG == 0 && AS % FX_PD == 0, "stages of whole row groups and weight rings");
+  const Dims &d = a.d;
+  const int lane = tid & 63, g = lane >> 4, col = lane & 15, M1 = d.M1, M2 = d.M2;
+  const int row = (tid >> 2) % R, bq = tid & 3, ag = (tid >> 2) / R;
+  const bool maker = ag < S::AG;
+  const int at = r0 + row < r1 ? a.atom_of_pos[r0 + row] : -1;
+  const Real *Ti = a.T + (int64_t)(at < 0 ? 0 : at) * M1 * 4;
+  v4 tb[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int b = 4 * bq + k;
+    const v4 v = *(const v4 *)(Ti + (b < M2 ? b : 0) * 4);
+    tb[k] = at >= 0 && b < M2 ? v : v4{0, 0, 0, 0};
+  }
+  const int nt = d.fw[1] / 16;
+  const Real *Wp = a.pack + a.pk.f[t][0];
+  auto wload = [&](int k, v4(&w)[C]) {
+    const int kc = k < M1 ? k : M1 - 1;
+#pragma unroll
+    for (int c = 0; c < C; ++c) w[c] = wblock(Wp + ((int64_t)kc * nt + ct[c]) * 256, lane);
+  };
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[r][c] = acc_t{0, 0, 0, 0};
+  constexpr int NG = AS / S::AG;  // rows of D a maker forms per stage
+  v4 ta[NG];
+  auto tload = [&](int st) {
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int k = st * AS + q * S::AG + ag;
+      const v4 v = *(const v4 *)(Ti + (k < M1 ? k : 0) * 4);
+      ta[q] = k < M1 ? v : v4{0, 0, 0, 0};
+    }
+  };
+  auto form = [&](Real *Ds) {
+    if (maker)
+#pragma unroll
+      for (int q = 0; q < NG; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          Ds[row * DS + 16 * (q * S::AG + ag) + 4 * bq + k] =
+              ta[q][0] * tb[k][0] + ta[q][1] * tb[k][1] + ta[q][2] * tb[k][2] + ta[q][3] * tb[k][3];
+  };
+  const int nst = (M1 + AS - 1) / AS;
+  v4 w[FX_PD][C];
+  tload(0);
+#pragma unroll
+  for (int k = 0; k < FX_PD; ++k) wload(k, w[k]);
+  form(X);
+  __syncthreads();
+  for (int st = 0; st < nst; ++st) {
+    const Real *Ds = X + (st & 1) * R * DS;
+    if (st + 1 < nst) tload(st + 1);
+#pragma unroll
+    for (int al = 0; al < AS; ++al) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        Real x[RT];
+#pragma unroll
+        for (int r = 0; r < RT; ++r) x[r] = Ds[(16 * r + col) * DS + 16 * al + MF<Real>::row(j, g)];
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc[r][c] = MF<Real>::mma(w[al % FX_PD][c][j], x[r], acc[r][c]);
+      }
+      wload(st * AS + al + FX_PD, w[al % FX_PD]);
+    }
+    if (st + 1 < nst) form(X + ((st + 1) & 1) * R * DS);
+    __syncthreads();
+  }
+}
+
+// FIRST = false: layer 0 has been evaluated by k_fitx_l0
+template <typename Real, int RT, bool FIRST>
+__global__ void __launch_bounds__(64 * NW, 1) k_fitx_fwd(FitFusedArgs<Real> a) {
+  typedef typename MF<Real>::acc acc_t;
+  typedef typename V4<Real>::t v4;
+  constexpr int R = 16 * RT;
   extern __shared__ __align__(16) unsigned char fitx_smem[];
   __shared__ Real es[NW][R];
   Real *X = (Real *)fitx_smem;
@@ -209,81 +290,13 @@ __global__ void __launch_bounds__(64 * NW, 1) k_fitx_fwd(FitFusedArgs<Real> a) {
   int64_t r0, r1;
   if (!fit_block(a, R, t, r0, r1) || a.atom_of_pos[r0] < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, col = lane & 15;
-  const int M1 = d.M1, M2 = d.M2;
   acc_t acc[RT][CT];
-  // ---- layer 0: K = (a, b), D formed in LDS stages of AS rows a ----
-  {
-    const int row = (tid >> 2) % R, bq = tid & 3, ag = (tid >> 2) / R;
-    const bool maker = ag < S::AG;
-    const int at = r0 + row < r1 ? a.atom_of_pos[r0 + row] : -1;
-    const Real *Ti = a.T + (int64_t)(at < 0 ? 0 : at) * M1 * 4;
-    v4 tb[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int b = 4 * bq + k;
-      const v4 v = *(const v4 *)(Ti + (b < M2 ? b : 0) * 4);
-      tb[k] = at >= 0 && b < M2 ? v : v4{0, 0, 0, 0};
-    }
+  if constexpr (FIRST) {
     const int nt = d.fw[1] / 16;
     int ct[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) ct[c] = wv * CT + c < nt ? wv * CT + c : nt - 1;
-    const Real *W = a.pack + a.pk.f[t][0];
-    auto wload = [&](int k, v4(&w)[CT]) {
-      const int kc = k < M1 ? k : M1 - 1;
-#pragma unroll
-      for (int c = 0; c < CT; ++c) w[c] = wblock(W + ((int64_t)kc * nt + ct[c]) * 256, lane);
-    };
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-      for (int c = 0; c < CT; ++c) acc[r][c] = acc_t{0, 0, 0, 0};
-    constexpr int NG = AS / S::AG;  // rows of D a maker forms per stage
-    v4 ta[NG];
-    auto tload = [&](int st) {
-#pragma unroll
-      for (int q = 0; q < NG; ++q) {
-        const int k = st * AS + q * S::AG + ag;
-        const v4 v = *(const v4 *)(Ti + (k < M1 ? k : 0) * 4);
-        ta[q] = k < M1 ? v : v4{0, 0, 0, 0};
-      }
-    };
-    auto form = [&](Real *Ds) {
-      if (maker)
-#pragma unroll
-        for (int q = 0; q < NG; ++q)
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-            Ds[row * DS + 16 * (q * S::AG + ag) + 4 * bq + k] =
-                ta[q][0] * tb[k][0] + ta[q][1] * tb[k][1] + ta[q][2] * tb[k][2] + ta[q][3] * tb[k][3];
-    };
-    const int nst = (M1 + AS - 1) / AS;
-    v4 w[FX_PD][CT];
-    tload(0);
-#pragma unroll
-    for (int k = 0; k < FX_PD; ++k) wload(k, w[k]);
-    form(X);
-    __syncthreads();
-    for (int st = 0; st < nst; ++st) {
-      const Real *Ds = X + (st & 1) * R * DS;
-      if (st + 1 < nst) tload(st + 1);
-#pragma unroll
-      for (int al = 0; al < AS; ++al) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          Real x[RT];
-#pragma unroll
-          for (int r = 0; r < RT; ++r) x[r] = Ds[(16 * r + col) * DS + 16 * al + MF<Real>::row(j, g)];
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) acc[r][c] = MF<Real>::mma(w[al % FX_PD][c][j], x[r], acc[r][c]);
-        }
-        wload(st * AS + al + FX_PD, w[al % FX_PD]);
-      }
-      if (st + 1 < nst) form(X + ((st + 1) & 1) * R * DS);
-      __syncthreads();
-    }
+    fitx_first<Real, RT, NW, CT>(a, t, r0, r1, ct, X, tid, acc);
   }
   // ---- epilogues and hidden layers ----
   const int XS = a.maxw + 1;
@@ -303,17 +316,19 @@ __global__ void __launch_bounds__(64 * NW, 1) k_fitx_fwd(FitFusedArgs<Real> a) {
       if (ct >= nt) continue;
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        v4 th;
+        v4 th, *const tp = (v4 *)(Tt + (((r0 >> 4) + r) * nt + ct) * 256 + lane * 4);
+        const bool done = !FIRST && l == 0;
+        if (done) th = *tp;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int o = 16 * ct + MF<Real>::row(q, g);
-          th[q] = MF<Real>::tanh_(acc[r][c][q] + bias[o]);
+          if (!done) th[q] = MF<Real>::tanh_(acc[r][c][q] + bias[o]);
           Real y = th[q];
           if (skip) y += X[(16 * r + col) * XS + o];
           acc[r][c][q] = y;
           if (last) ep[r] += y * wo[o];
         }
-        if (r0 + 16 * r < r1) *(v4 *)(Tt + (((r0 >> 4) + r) * nt + ct) * 256 + lane * 4) = th;
+        if (!done && r0 + 16 * r < r1) *tp = th;
       }
     }
     if (last) {
@@ -354,10 +369,116 @@ __global__ void __launch_bounds__(64 * NW, 1) k_fitx_fwd(FitFusedArgs<Real> a) {
   }
 }
 
+// Layer 0 alone, four column tiles a workgroup (blockIdx.y: which), for
+// systems of so few rows that one workgroup per 16 rows leaves most CUs idle.
+constexpr int FS_W = 4;
+template <typename Real>
+__global__ void __launch_bounds__(64 * FS_W, 1) k_fitx_l0(FitFusedArgs<Real> a) {
+  typedef FwdShape<Real, 1, FS_W> S;
+  typedef typename V4<Real>::t v4;
+  __shared__ __align__(16) Real X[2 * S::R * S::DS];
+  int t;
+  int64_t r0, r1;
+  if (!fit_block(a, S::R, t, r0, r1) || a.atom_of_pos[r0] < 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, nt = a.d.fw[1] / 16, tile = blockIdx.y * FS_W + (tid >> 6);
+  const int ct[1] = {tile < nt ? tile : nt - 1};
+  typename MF<Real>::acc acc[1][1];
+  fitx_first<Real, 1, FS_W, 1>(a, t, r0, r1, ct, X, tid, acc);
+  if (tile >= nt) return;
+  const Real *bias = a.fwt + a.fo.b[t][0];
+  v4 th;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) th[q] = MF<Real>::tanh_(acc[0][0][q] + bias[16 * tile + MF<Real>::row(q, g)]);
+  *(v4 *)(a.Tt[1] + ((r0 >> 4) * nt + tile) * 256 + lane * 4) = th;
+}
+
 // ---------------------------------------------------------------------------
 // backward
 // ---------------------------------------------------------------------------
-template <typename Real, int RT>
+// dE/dD, one row a of D at a time (this wave: a = a0, a0 + step, ..): lane (g, n)
+// gets b = row(q, g) of row n.  X: gz of layer 0, row stride XS; Tl: T_<, at the
+// end the sums over the workgroup's rows a of dD[a][b] T[a].
+template <typename Real, int RT, int W>
+__device__ inline void fitx_last(const FitFusedArgs<Real> &a, int t, int64_t r0, int64_t r1, const Real *X, int XS, Real *Tl,
+                                 int a0, int step, int tid) {
+  typedef typename MF<Real>::acc acc_t;
+  typedef typename V4<Real>::t v4;
+  const Dims &d = a.d;
+  const int lane = tid & 63, wv = tid >> 6, g = lane >> 4, col = lane & 15, M1 = d.M1;
+  int at[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) at[r] = r0 + 16 * r + col < r1 ? a.atom_of_pos[r0 + 16 * r + col] : -1;
+  const int nk = d.fw[1] / 16;
+  const Real *W0 = a.pack + a.pk.b[t][0];
+  const Real *xr = X + col * XS;
+  const Real sc = (Real)d.inv_nc;
+  v4 low[RT][4];  // sum over this wave's a of dD[a][b = row(q, g)] T[a]
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) low[r][q] = v4{0, 0, 0, 0};
+  // the wave's weights are one stream over (a, chunk): FX_PD of them in flight
+  v4 w[FX_PD];
+  int wa = a0, wk = 0;
+  auto wload = [&](v4 &q) {
+    q = wblock(W0 + ((int64_t)(wa < M1 ? wa : M1 - 1) * nk + wk) * 256, lane);
+    if (++wk == nk) {
+      wk = 0;
+      wa += step;
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < FX_PD; ++k) wload(w[k]);
+  for (int ar = a0; ar < M1; ar += step) {
+    acc_t z[RT], z2[RT];
+    v4 ta[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      z[r] = z2[r] = acc_t{0, 0, 0, 0};
+      ta[r] = *(const v4 *)(a.T + ((int64_t)(at[r] < 0 ? 0 : at[r]) * M1 + ar) * 4);
+    }
+    for (int kc = 0; kc < nk; ++kc) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          acc_t &zj = j & 1 ? z2[r] : z[r];
+          zj = MF<Real>::mma(w[0][j], xr[16 * r * XS + 16 * kc + MF<Real>::row(j, g)], zj);
+        }
+#pragma unroll
+      for (int k = 0; k + 1 < FX_PD; ++k) w[k] = w[k + 1];
+      wload(w[FX_PD - 1]);
+    }
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      z[r] += z2[r];
+      v4 p = {0, 0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        p += z[r][q] * *(const v4 *)(Tl + ((16 * r + col) * 16 + MF<Real>::row(q, g)) * 4);
+        low[r][q] += z[r][q] * ta[r];
+      }
+      const Real v = group_columns<Real>(p, g);
+      if (at[r] >= 0) a.dT[((int64_t)at[r] * M1 + ar) * 4 + g] = v * sc;
+    }
+  }
+  // the sums over a of the waves, in order, into the LDS area of T_<
+  __syncthreads();
+  for (int wi = 0; wi < W; ++wi) {
+    if (wi == wv)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          v4 *o = (v4 *)(Tl + ((16 * r + col) * 16 + MF<Real>::row(q, g)) * 4);
+          *o = wi == 0 ? low[r][q] : *o + low[r][q];
+        }
+    __syncthreads();
+  }
+}
+
+// LAST = false: leaves gz of layer 0 in a.gz for k_fitx_d0
+template <typename Real, int RT, bool LAST>
 __global__ void __launch_bounds__(64 * NW, 1) k_fitx_bwd(FitFusedArgs<Real> a) {
   typedef typename MF<Real>::acc acc_t;
   typedef typename V4<Real>::t v4;
@@ -407,8 +528,12 @@ __global__ void __launch_bounds__(64 * NW, 1) k_fitx_bwd(FitFusedArgs<Real> a) {
         const int64_t rt = (r0 >> 4) + (r0 + 16 * r < r1 ? r : 0);
         const v4 th = *(const v4 *)(Tt + (rt * nt + ct) * 256 + lane * 4);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          X[(16 * r + col) * XS + 16 * ct + MF<Real>::row(q, g)] = gy[r][c][q] * (Real(1) - th[q] * th[q]);
+        for (int q = 0; q < 4; ++q) {
+          const int o = 16 * ct + MF<Real>::row(q, g);
+          const Real gz = gy[r][c][q] * (Real(1) - th[q] * th[q]);
+          if (!LAST && l == 0) a.gz[(r0 + 16 * r + col) * out + o] = gz;
+          else X[(16 * r + col) * XS + o] = gz;
+        }
       }
     }
     __syncthreads();
@@ -428,77 +553,9 @@ __global__ void __launch_bounds__(64 * NW, 1) k_fitx_bwd(FitFusedArgs<Real> a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) gy[r][c][q] = skip ? acc[r][c][q] + gy[r][c][q] : acc[r][c][q];
   }
-  // dE/dD, one row a of D at a time: lane (g, n) gets b = row(q, g) of row n
-  int at[RT];
-#pragma unroll
-  for (int r = 0; r < RT; ++r) at[r] = r0 + 16 * r + col < r1 ? a.atom_of_pos[r0 + 16 * r + col] : -1;
-  const int nk = d.fw[1] / 16;
-  const Real *W0 = a.pack + a.pk.b[t][0];
-  const Real *xr = X + col * XS;
+  if constexpr (!LAST) return;
+  fitx_last<Real, RT, NW>(a, t, r0, r1, X, XS, Tl, wv, NW, tid);
   const Real sc = (Real)d.inv_nc;
-  v4 low[RT][4];  // sum over this wave's a of dD[a][b = row(q, g)] T[a]
-#pragma unroll
-  for (int r = 0; r < RT; ++r)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) low[r][q] = v4{0, 0, 0, 0};
-  // the wave's weights are one stream over (a, chunk): FX_PD of them in flight
-  v4 w[FX_PD];
-  int wa = wv, wk = 0;
-  auto wload = [&](v4 &q) {
-    q = wblock(W0 + ((int64_t)(wa < M1 ? wa : M1 - 1) * nk + wk) * 256, lane);
-    if (++wk == nk) {
-      wk = 0;
-      wa += NW;
-    }
-  };
-#pragma unroll
-  for (int k = 0; k < FX_PD; ++k) wload(w[k]);
-  for (int ar = wv; ar < M1; ar += NW) {
-    acc_t z[RT], z2[RT];
-    v4 ta[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      z[r] = z2[r] = acc_t{0, 0, 0, 0};
-      ta[r] = *(const v4 *)(a.T + ((int64_t)(at[r] < 0 ? 0 : at[r]) * M1 + ar) * 4);
-    }
-    for (int kc = 0; kc < nk; ++kc) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-          acc_t &zj = j & 1 ? z2[r] : z[r];
-          zj = MF<Real>::mma(w[0][j], xr[16 * r * XS + 16 * kc + MF<Real>::row(j, g)], zj);
-        }
-#pragma unroll
-      for (int k = 0; k + 1 < FX_PD; ++k) w[k] = w[k + 1];
-      wload(w[FX_PD - 1]);
-    }
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      z[r] += z2[r];
-      v4 p = {0, 0, 0, 0};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        p += z[r][q] * *(const v4 *)(Tl + ((16 * r + col) * 16 + MF<Real>::row(q, g)) * 4);
-        low[r][q] += z[r][q] * ta[r];
-      }
-      const Real v = group_columns<Real>(p, g);
-      if (at[r] >= 0) a.dT[((int64_t)at[r] * M1 + ar) * 4 + g] = v * sc;
-    }
-  }
-  // the sums over a of the waves, in order, into the LDS area of T_<
-  __syncthreads();
-  for (int wi = 0; wi < NW; ++wi) {
-    if (wi == wv)
-#pragma unroll
-      for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          v4 *o = (v4 *)(Tl + ((16 * r + col) * 16 + MF<Real>::row(q, g)) * 4);
-          *o = wi == 0 ? low[r][q] : *o + low[r][q];
-        }
-    __syncthreads();
-  }
   for (int o = tid; o < R * M2; o += 64 * NW) {
     const int row = o / M2, b = o % M2;
     const int i = r0 + row < r1 ? a.atom_of_pos[r0 + row] : -1;
@@ -508,18 +565,73 @@ __global__ void __launch_bounds__(64 * NW, 1) k_fitx_bwd(FitFusedArgs<Real> a) {
   }
 }
 
-template <typename Real, int RT>
+// dE/dT from gz of layer 0, the rows a of D dealt to gridDim.y workgroups of
+// 16 rows; their sums over a go to a.low and are added by k_fitx_low.
+template <typename Real>
+__global__ void __launch_bounds__(64 * FS_W, 1) k_fitx_d0(FitFusedArgs<Real> a) {
+  typedef typename V4<Real>::t v4;
+  __shared__ __align__(16) Real X[16 * (16 * FITX_TILES + 1)];
+  __shared__ __align__(32) Real Tl[16 * 16 * 4];
+  const Dims &d = a.d;
+  int t;
+  int64_t r0, r1;
+  if (!fit_block(a, 16, t, r0, r1) || a.atom_of_pos[r0] < 0) return;
+  const int tid = threadIdx.x, w1 = d.fw[1], M1 = d.M1, M2 = d.M2, XS = w1 + 1;
+  for (int o = tid; o < 16 * w1; o += 64 * FS_W) X[o / w1 * XS + o % w1] = a.gz[(r0 + o / w1) * w1 + o % w1];
+  for (int o = tid; o < 16 * 16; o += 64 * FS_W) {
+    const int b = o & 15, at = a.atom_of_pos[r0 + (o >> 4)];
+    v4 v = *(const v4 *)(a.T + ((int64_t)(at < 0 ? 0 : at) * M1 + (b < M2 ? b : 0)) * 4);
+    if (at < 0 || b >= M2) v = v4{0, 0, 0, 0};
+    *(v4 *)(Tl + o * 4) = v;
+  }
+  __syncthreads();
+  fitx_last<Real, 1, FS_W>(a, t, r0, r1, X, XS, Tl, blockIdx.y * FS_W + (tid >> 6), FS_W * gridDim.y, tid);
+  for (int o = tid; o < 16 * 16; o += 64 * FS_W)
+    *(v4 *)(a.low + ((int64_t)blockIdx.y * a.rows + r0) * 64 + o * 4) = *(const v4 *)(Tl + o * 4);
+}
+
+// dE/dT of the first M2 rows += the workgroups' sums, in order
+template <typename Real>
+__global__ void k_fitx_low(FitFusedArgs<Real> a, int ny) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, row = q >> 6;
+  const int b = (int)(q >> 2) & 15;
+  if (row >= a.rows || row >= a.type_start[a.d.ntypes] || b >= a.d.M2) return;
+  const int i = a.atom_of_pos[row];
+  if (i < 0) return;
+  Real v = 0;
+  for (int y = 0; y < ny; ++y) v += a.low[(int64_t)y * a.rows * 64 + q];
+  a.dT[((int64_t)i * a.d.M1 + b) * 4 + (q & 3)] += v * (Real)a.d.inv_nc;
+}
+
+template <typename Real, int RT, bool ALL = true>
 static void launch_fitx(hipStream_t s, const FitFusedArgs<Real> &a, int pass) {
   constexpr int R = 16 * RT;
   const unsigned grid = (unsigned)(a.rows / R + 2 * a.d.ntypes);
   if (pass == 1) {
-    const size_t lds = FwdShape<Real, RT>::lds(a.maxw);
-    (void)hipFuncSetAttribute((const void *)k_fitx_fwd<Real, RT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((k_fitx_fwd<Real, RT>), dim3(grid), dim3(64 * NW), lds, s, a);
+    const size_t lds = FwdShape<Real, RT, NW>::lds(a.maxw);
+    (void)hipFuncSetAttribute((const void *)k_fitx_fwd<Real, RT, ALL>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)lds);
+    hipLaunchKernelGGL((k_fitx_fwd<Real, RT, ALL>), dim3(grid), dim3(64 * NW), lds, s, a);
   } else if constexpr (RT <= 2) {
     const size_t lds = sizeof(Real) * ((size_t)R * (a.maxw + 1) + (size_t)R * 64);
-    (void)hipFuncSetAttribute((const void *)k_fitx_bwd<Real, RT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((k_fitx_bwd<Real, RT>), dim3(grid), dim3(64 * NW), lds, s, a);
+    (void)hipFuncSetAttribute((const void *)k_fitx_bwd<Real, RT, ALL>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)lds);
+    hipLaunchKernelGGL((k_fitx_bwd<Real, RT, ALL>), dim3(grid), dim3(64 * NW), lds, s, a);
+  }
+}
+
+// 16 rows at a time with the wide layer 0 spread over FS_Y workgroups each
+constexpr int FS_Y = 4;
+template <typename Real>
+static void launch_fitx_spread(hipStream_t s, const FitFusedArgs<Real> &a, int pass) {
+  const unsigned gx = (unsigned)(a.rows / 16 + 2 * a.d.ntypes);
+  if (pass == 1) {
+    hipLaunchKernelGGL(k_fitx_l0<Real>, dim3(gx, (unsigned)(a.d.fw[1] / 16 + FS_W - 1) / FS_W), dim3(64 * FS_W), 0, s, a);
+    launch_fitx<Real, 1, false>(s, a, pass);
+  } else {
+    launch_fitx<Real, 1, false>(s, a, pass);
+    hipLaunchKernelGGL(k_fitx_d0<Real>, dim3(gx, FS_Y), dim3(64 * FS_W), 0, s, a);
+    hipLaunchKernelGGL(k_fitx_low<Real>, dim3((unsigned)((a.rows * 64 + 255) / 256)), dim3(256), 0, s, a, FS_Y);
   }
 }
 
@@ -736,6 +848,13 @@ static void launch_fitr_bwd(hipStream_t s, const FitFusedArgs<Real> &a) {
   hipLaunchKernelGGL(k_fitr_bwd<Real>, dim3((unsigned)(a.rows / FR_ROWS)), dim3(64 * FR_WAVES), lds, s, a);
 }
 
+// Atoms up to which layer 0 is spread: one workgroup per 16 rows leaves CUs
+// idle (us, forward + backward, as one kernel each | spread: FP64 192 atoms
+// 94 + 106 | 61 + 74, 1,367 97 + 110 | 79 + 85, 2,048 101 + 113 | 92 + 102,
+// 3,000 103 + 116 | 112 + 107; FP32 192 56 + 64 | 40 + 47, 2,048 60 + 70 |
+// 60 + 70).
+constexpr int64_t FIT_SPREAD = 2048;
+
 // Time of a launch whose workgroups take R atoms each: the rounds that 256
 // CUs need for them, times a round's time (us, 1600-240-240-240).
 static int64_t fit_rounds(int64_t n, int R) { return (n + 256 * R - 1) / (256 * R); }
@@ -753,6 +872,10 @@ static int64_t fit_rounds(int64_t n, int R) { return (n + 256 * R - 1) / (256 * 
 template <typename Real>
 void launch_fit_fused(hipStream_t s, const FitFusedArgs<Real> &a, int64_t n, int pass) {
   constexpr bool F64 = sizeof(Real) == 8;
+  if (n <= FIT_SPREAD && a.gz) {
+    launch_fitx_spread(s, a, pass);
+    return;
+  }
   const int64_t r1 = fit_rounds(n, 16), r2 = fit_rounds(n, 32), r4 = fit_rounds(n, 64);
   if (pass == 1) {
     const int64_t t1 = r1 * (F64 ? 100 : 56), t2 = r2 * (F64 ? 176 : 95);

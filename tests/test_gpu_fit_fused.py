@@ -53,7 +53,9 @@ def _cell():
 
 
 # hidden widths, M2, repeats of the cell
-CASES = [((240, 240, 240), 16, (1, 1, 1)),     # 187 atoms: 16 rows
+CASES = [((240, 240, 240), 16, (1, 1, 1)),     # 187 atoms: 16 rows, layer 0 spread over workgroups
+         ((240, 240), 7, (1, 1, 1)),           # ... D too narrow to hold what the spread passes on
+         ((240, 240, 240), 16, (4, 4, 1)),     # 2,992: 16 rows, one kernel a pass
          ((240, 240, 240), 16, (5, 5, 1)),     # 4,675: 32 rows
          ((240, 240, 240), 16, (10, 7, 1)),    # 13,090: 64 rows (FP64) and the row-wave backward
          ((240,), 7, (10, 7, 1)),              # ... of one layer, fewer columns of D
