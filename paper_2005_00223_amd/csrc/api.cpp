@@ -1431,16 +1431,44 @@ void eval_judge(dp_ctx *c, int64_t n) {
   c->timing = tim;
 }
 
-void build_lists(dp_ctx *c, int64_t n, const CellGrid &g, double rlist, const uint32_t *cond) {
+void build_cells(dp_ctx *c, int64_t n, const CellGrid &g, const uint32_t *cond) {
   Workspace &w = c->ws;
   // the cell-ordered positions borrow xref: under cond the caller copies the
   // new reference positions there after the build, and no one else reads it
   launch_cells(c->stream, n, w.xw, g, w.cell_of, w.cell_start, w.cell_fill, w.cell_atoms, w.cell_code,
                (CellPos *)w.xref, w.scan_tmp, cond);
+}
+
+// Candidate lists of the first n atoms from the cells of grid g.
+void build_candidates(dp_ctx *c, int64_t n, const CellGrid &g, double rlist, const uint32_t *cond) {
+  Workspace &w = c->ws;
   c->cgrid = g;
   c->cgrid_ok = true;
   launch_candidates(c->stream, n, w.xw, g, w.cell_start, (const CellPos *)w.xref, rlist, w.cand_cap, w.cand, w.cand_n,
                     &w.status->flags, cond);
+}
+
+void build_lists(dp_ctx *c, int64_t n, const CellGrid &g, double rlist, const uint32_t *cond) {
+  build_cells(c, n, g, cond);
+  build_candidates(c, n, g, rlist, cond);
+}
+
+// Wrapped positions of n atoms, rows of the first n_rows, cells and their
+// candidates: a single evaluation's lists.
+void prepare_frame(dp_ctx *c, int64_t n, int64_t n_rows, const double *coords, const int32_t *types, const double *L,
+                   const CellGrid &g, double rlist) {
+  Workspace &w = c->ws;
+  const Dims &d = c->dims;
+  hipStream_t s = c->stream;
+  if (!launch_prep_small(s, n, n_rows, coords, types, d.ntypes, g, w.xw, &w.status->flags, w.type_count, w.type_start,
+                         w.pos_of_atom, w.atom_of_pos, eval_rows(c, n_rows), w.cell_of, w.cell_start, w.cell_atoms,
+                         w.cell_code, (CellPos *)w.xref)) {
+    launch_wrap(s, n, coords, types, d.ntypes, L, w.xw, &w.status->flags);
+    launch_type_sort(s, n_rows, w.xw, d.ntypes, w.blk_counts, w.type_count, w.type_start, w.pos_of_atom, w.atom_of_pos,
+                     w.rows_cap);
+    build_cells(c, n, g, nullptr);
+  }
+  build_candidates(c, n_rows, g, rlist, nullptr);
 }
 
 int read_status(dp_ctx *c) {
@@ -1979,10 +2007,7 @@ static int compute_impl(dp_ctx *c, int64_t n, const double *coords, const int32_
     tmark(c, 0);
     hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, s, w.status, 0u);
     if (n > 0) {
-      launch_wrap(s, n, coords, types, d.ntypes, L, w.xw, &w.status->flags);
-      launch_type_sort(s, n, w.xw, d.ntypes, w.blk_counts, w.type_count, w.type_start, w.pos_of_atom,
-                       w.atom_of_pos, w.rows_cap);
-      build_lists(c, n, g, rlist, nullptr);
+      prepare_frame(c, n, n, coords, types, L, g, rlist);
       eval_forward(c, n, L);
       if (backward) eval_backward(c, n, F, w.virial);
     } else {
@@ -2062,17 +2087,9 @@ static int compute_local_impl(dp_ctx *c, int64_t n_local, int64_t n, const doubl
     tmark(c, 0);
     hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, s, w.status, 0u);
     if (n_local > 0) {
-      launch_wrap(s, n, coords, types, d.ntypes, L, w.xw, &w.status->flags);
-      // rows (the fitting net's and the embedding kernels') for the centres only
-      launch_type_sort(s, n_local, w.xw, d.ntypes, w.blk_counts, w.type_count, w.type_start, w.pos_of_atom,
-                       w.atom_of_pos, w.rows_cap);
-      // the cell list holds every atom, candidate lists the centres
-      launch_cells(s, n, w.xw, g, w.cell_of, w.cell_start, w.cell_fill, w.cell_atoms, w.cell_code,
-                   (CellPos *)w.xref, w.scan_tmp, nullptr);
-      c->cgrid = g;
-      c->cgrid_ok = true;
-      launch_candidates(s, n_local, w.xw, g, w.cell_start, (const CellPos *)w.xref, rlist, w.cand_cap, w.cand, w.cand_n,
-                        &w.status->flags, nullptr);
+      // rows (the fitting net's and the embedding kernels') and candidate
+      // lists for the centres only; the cell list holds every atom
+      prepare_frame(c, n, n_local, coords, types, L, g, rlist);
       c->n_force = n;
       eval_forward(c, n_local, L);
       eval_backward(c, n_local, F, w.virial);

@@ -92,6 +92,12 @@ void launch_type_sort(hipStream_t s, int64_t n, const double4 *xw, int ntypes, i
 void launch_cells(hipStream_t s, int64_t n, const double4 *xw, const CellGrid &g, int32_t *cell_of,
                   int32_t *cell_start, int32_t *cell_fill, int32_t *cell_atoms, uint32_t *cell_code,
                   CellPos *xs, int32_t *scan_tmp, const uint32_t *cond);
+// the three above for a small system in one kernel (rows for the first n_rows
+// atoms); false, and nothing launched, when the system is not small
+bool launch_prep_small(hipStream_t s, int64_t n, int64_t n_rows, const double *coords, const int32_t *types, int ntypes,
+                       const CellGrid &g, double4 *xw, uint32_t *flags, int32_t *type_count, int32_t *type_start,
+                       int32_t *pos_of_atom, int32_t *atom_of_pos, int64_t rows, int32_t *cell_of,
+                       int32_t *cell_start, int32_t *cell_atoms, uint32_t *cell_code, CellPos *xs);
 void launch_candidates(hipStream_t s, int64_t n, const double4 *xw, const CellGrid &g, const int32_t *cell_start,
                        const CellPos *xs, double rlist, int cand_cap, int32_t *cand, int32_t *cand_n,
                        uint32_t *flags, const uint32_t *cond);
