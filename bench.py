@@ -97,8 +97,8 @@ PHASE_KERNEL = {
     ("embed_fwd", False): ("k_embed_fwd_mix<25, 50, 100, 0, 0>", "k_embed_mix"),
     ("fit_fwd", True): ("k_fit_fwd<0, 15>", "k_fit_mix"),
     ("fit_fwd", False): ("k_fit_fwd<0, 15>", "k_fit_mix"),
-    ("fit_bwd", True): ("k_fit_bwd<0, 15>", "k_fit_mix"),
-    ("fit_bwd", False): ("k_fit_bwd<0, 15>", "k_fit_mix"),
+    ("fit_bwd", True): ("k_fit_bwd<0, 15, false>", "k_fit_mix"),
+    ("fit_bwd", False): ("k_fit_bwd<0, 15, false>", "k_fit_mix"),
     ("format", True): ("k_format", "k_nlist"),
     ("format", False): ("k_format", "k_nlist"),
     ("env", True): ("k_env<HIP_vector_type<float, 4u> >", "k_env"),
