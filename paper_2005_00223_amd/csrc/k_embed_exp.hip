@@ -26,8 +26,8 @@
 // Measured, 32,000 copper atoms (5.8 million pairs), the layer kernels before
 // and these now: FP64 forward 5.30 ms -> 0.12 (k_exp_pair 0.09, k_exp_desc
 // 0.03), backward 8.05 ms -> 0.30 (k_exp_adj 0.04, k_exp_force 0.26); FP32
-// forward 3.19 ms -> 0.08, backward 6.03 ms -> 0.21.  FP16, 62,565 centres:
-// forward 2.18 ms -> 0.15, backward 3.53 ms -> 0.38.
+// forward 3.19 ms -> 0.08, backward 6.03 ms -> 0.19.  FP16, 62,565 centres:
+// forward 2.18 ms -> 0.15, backward 3.53 ms -> 0.34.
 // The pair kernels wait on latency (atom -> list -> positions -> pieces -> M)
 // more than they compute: atom data come by scalar loads, pieces are found
 // once per neighbour from lanes, positions and M are loaded ahead
@@ -548,14 +548,18 @@ __global__ void __launch_bounds__(64) k_exp_adj(ExpArgs<Real> a) {
 // order, where nothing merges, cost what they did (1,441 against 1,439 us for
 // an FP32 evaluation).  318 -> 188 us FP32, 335 -> 258 FP64, 62,565 centres
 // 600 -> 339; 8 rows 204 us, 32 rows 224; a workgroup per cell of the cell
-// list with sums addressed by cell 208 to 380 (cells differ in size).
+// list with sums addressed by cell 208 to 380 (cells differ in size).  What is
+// left waits on latency, so waves count: in FP32 the workgroups' LDS and 128
+// registers (nine of them spilled) let four share a CU instead of three, 188 ->
+// 166 us and 339 -> 298; in FP64 a third wave per SIMD spills 32 (258 -> 302
+// us) and is not taken.
 template <typename Real, bool MERGE>
-__global__ void __launch_bounds__(64 * EXP_WAVES, sizeof(Real) == 8 ? 2 : 3) k_exp_force(ExpArgs<Real> a) {
+__global__ void __launch_bounds__(64 * EXP_WAVES, sizeof(Real) == 8 ? 2 : MERGE ? 4 : 3) k_exp_force(ExpArgs<Real> a) {
   constexpr int K = ExpK<Real>::K;
   constexpr int MS = EXP_KP + 2;  // row stride of a component's coefficients in LDS
-  __shared__ __align__(16) Real Rs[EXP_WAVES][64 * 4];
   __shared__ __align__(16) Real Ms[EXP_WAVES][8 * MS];
-  __shared__ __align__(16) double Fs[EXP_WAVES][64 * 4];
+  // environment rows, then dE/dR (four Real a neighbour), then forces (three double)
+  __shared__ __align__(16) double Fs[EXP_WAVES][sizeof(Real) == 8 ? 64 * 4 : 64 * 3];
   __shared__ double vred[EXP_WAVES][9];
   __shared__ int32_t key[MERGE ? EXP_HASH : 1];       // atom of a sum, or -1
   __shared__ double facc[MERGE ? 3 * EXP_HASH : 1];
@@ -563,8 +567,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, sizeof(Real) == 8 ? 2 : 3) k_e
   const Dims &d = a.d;
   // uniform over the wave: the atom's data come by scalar loads
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 3;
-  Real *Rw = Rs[wv], *Mw = Ms[wv];
+  Real *Mw = Ms[wv];
   double *Fw = Fs[wv];
+  Real *Rw = (Real *)Fw;
   const int P = a.tab.P;
   const double inv_w = 1.0 / (d.rcut - d.rcut_smth);
   double vir[9];
@@ -670,8 +675,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, sizeof(Real) == 8 ? 2 : 3) k_e
           Rw[nl * 4 + c] = c == 0 ? ga + e : ga;
         }
         wave_sync();
+        const double g0 = Rw[lane * 4], g1 = Rw[lane * 4 + 1], g2 = Rw[lane * 4 + 2], g3 = Rw[lane * 4 + 3];
+        wave_sync();
         if (in) {
-          const double g0 = Rw[lane * 4], g1 = Rw[lane * 4 + 1], g2 = Rw[lane * 4 + 2], g3 = Rw[lane * 4 + 3];
           if (a.net_deriv) {
             double *nd = a.net_deriv + (base + q) * 4;
             nd[0] = g0;
@@ -691,9 +697,9 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, sizeof(Real) == 8 ? 2 : 3) k_e
           fx += gx;
           fy += gy;
           fz += gz;
-          Fw[lane * 4 + 0] = -gx;
-          Fw[lane * 4 + 1] = -gy;
-          Fw[lane * 4 + 2] = -gz;
+          Fw[lane * 3 + 0] = -gx;
+          Fw[lane * 3 + 1] = -gy;
+          Fw[lane * 3 + 2] = -gz;
           vir[0] = fma(-gx, g.dx, vir[0]);
           vir[1] = fma(-gx, g.dy, vir[1]);
           vir[2] = fma(-gx, g.dz, vir[2]);
@@ -710,7 +716,7 @@ __global__ void __launch_bounds__(64 * EXP_WAVES, sizeof(Real) == 8 ? 2 : 3) k_e
         for (int sub = 0; sub < 4 && sub * 16 < left; ++sub) {
           const int nl = sub * 16 + (lane >> 2);
           const int jn = __shfl(j, nl), sl = MERGE ? __shfl(jsl, nl) : -1;
-          if (c < 3 && nl < left) add(jn, sl, c, Fw[nl * 4 + c]);
+          if (c < 3 && nl < left) add(jn, sl, c, Fw[nl * 3 + c]);
         }
       }
     }

@@ -872,6 +872,7 @@ static int64_t fit_rounds(int64_t n, int R) { return (n + 256 * R - 1) / (256 * 
 template <typename Real>
 void launch_fit_fused(hipStream_t s, const FitFusedArgs<Real> &a, int64_t n, int pass) {
   constexpr bool F64 = sizeof(Real) == 8;
+  if (a.rows <= 0) return;
   if (n <= FIT_SPREAD && a.gz) {
     launch_fitx_spread(s, a, pass);
     return;
