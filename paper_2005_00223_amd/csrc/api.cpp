@@ -400,7 +400,10 @@ size_t ws_carve(const dp_ctx *c, Workspace &w, int64_t nn, int64_t nc, int cc, b
     // in float under DP_MIX_FP32 (the pointers are then read as float)
     add((void **)&w.T, rb * nn * d.M1 * 4);
     add((void **)&w.D, rb * rows * d.M1 * d.M2);
-    add((void **)&w.dD, rb * rows * d.M1 * d.M2);
+    // dE/dD, or (fused fitting kernels, expansions only) dE/dT [nn][M1][4], which
+    // is the larger of the two below M2 = 4
+    const size_t nd_d = (size_t)rows * d.M1 * d.M2, nd_t = (size_t)nn * d.M1 * 4;
+    add((void **)&w.dD, rb * (exp ? std::max(nd_d, nd_t) : nd_d));
     for (int l = 1; l <= d.n_fit; ++l) {
       add((void **)&w.Y[l], rb * rows * d.fw[l]);
       add((void **)&w.Tt[l], rb * rows * d.fw[l]);
