@@ -192,6 +192,7 @@ struct Workspace {
   unsigned long long *exp_mask = nullptr;
   void *exp_hm = nullptr;
   int seg = 0;
+  bool env_ok = false;  // the environment rows are those of the current lists
   int prec = -1;  // precision the buffers were laid out for
   DevStatus *status;
 };
@@ -392,7 +393,7 @@ size_t ws_carve(const dp_ctx *c, Workspace &w, int64_t nn, int64_t nc, int cc, b
   if (exp) {
     const size_t per = (mixed || f32 ? sizeof(float) : sizeof(double)) * 2 * EXP_KP * 4;  // M of one segment
     if (off - env0 < per * EXP_SEG * nn) add(&w.exp_hm, per * EXP_SEG * nn);
-    else if (base) w.exp_hm = base + env0;
+    else if (base) w.exp_hm = base + env0;  // an evaluation on the expansions takes the rows' place
     w.seg = EXP_SEG;
     add((void **)&w.exp_mask, sizeof(unsigned long long) * nn);
   }
@@ -1094,6 +1095,7 @@ void eval_lists(dp_ctx *c, int64_t n, const double L[3]) {
                 w.status->max_real, &w.status->flags, fused ? w.rt32 : nullptr);
   tmark(c, 2);
   if (!fused && !exp) launch_env(s, n, w.xw, d, L, w.nlist, w.nreal, w.rt, w.rt32, w.dr);
+  w.env_ok = !exp;
   tmark(c, 3);
 }
 
@@ -1255,6 +1257,10 @@ void eval_nets_fwd(dp_ctx *c, int64_t n, double *E) {
   const int64_t rows = eval_rows(c, n);
   c->exp_now = use_exp(c);
   c->d_of_T = use_fused(c);
+  // the layers read the rows; a judge's nets may meet lists that were made for
+  // nets on expansions, or rows whose place those have taken
+  if (!c->exp_now && !w.env_ok) launch_env(s, n, w.xw, c->dims, c->box_L, w.nlist, w.nreal, w.rt, w.rt32, w.dr);
+  w.env_ok = !c->exp_now;
   if (c->exp_now) {
     if (c->precision == DP_FP64) launch_exp_fwd<double>(s, exp_args<double>(c, rows, nullptr));
     else launch_exp_fwd<float>(s, exp_args<float>(c, rows, nullptr));

@@ -97,3 +97,60 @@ def test_fewer_columns_than_components(M2, fit, prec):
     X, T, B, copies, order = _repeat(x, t, box, (5, 5, 1))
     say(f"[routes] M2 {M2}, fitting {fit}, {prec}: {len(X)} atoms")
     _compare(_model(spec, prec).compute(X, T, B), r, prec, f"M2 {M2}", copies, order)
+
+
+def _rough_copper(scale=24.0):
+    """The copper model with first embedding layers too steep for an
+    expansion in any precision: its layers are evaluated."""
+    spec = synth.copper_model(1)
+    for row in spec.emb_W:
+        for W in row:
+            W[0] = W[0] * scale
+    return spec
+
+
+def _md(m, w, nsteps, prec):
+    t = w["types"]
+    x = torch.tensor(w["coords"], dtype=torch.float64, device="cuda")
+    v = torch.tensor(synth.maxwell_boltzmann(w["masses"][t], 300.0, w["vseed"]), dtype=torch.float64, device="cuda")
+    return m.md_run(x, v, t, w["box"], w["masses"], 0.2, nsteps, skin=0.3, thermo_every=10).cpu().numpy()
+
+
+# judge over all atoms, and over a cube confirmed by all
+@pytest.mark.parametrize("name,side", [("cu_cells5", 0.0), ("cu_cells9", 10.0)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_judge_of_a_teacher_without_expansion(prec, name, side):
+    """A student on an expansion judged by a teacher on its layers: a student
+    with zero outputs (no forces) is rejected at step 0 with the RMS of the
+    teacher's forces, and the run is the teacher's from there on; a kept
+    student's RMSE is that of the two nets' own evaluations.  RMSE within 1e-6
+    relative (atomics' order); trajectories 1e-9 (FP32 1e-7: a last bit of an
+    s may round otherwise)."""
+    w = synth.workload(name)
+    teacher = _rough_copper()
+    n = len(w["types"])
+    mt = _model(teacher, prec)
+    _, ft, _ = mt.compute(w["coords"], w["types"], w["box"])
+    r = _oracle(teacher, w["coords"], w["types"], w["box"], prec)
+    df = np.abs(ft.cpu().numpy() - r["force"]).max() / np.abs(r["force"]).max()
+    say(f"[routes] judge {name} {prec}: teacher F {df:.2e}")
+    assert df <= BARS[prec][0]
+    want = _md(mt, w, 20, prec)
+    P = synth.random_student_params(teacher, 31)
+    zero = P.copy()
+    zero[:, -33 * teacher.M1:] = 0.0
+    for params, keep in ((zero, False), (P, True)):
+        m = _model(teacher, prec)
+        m.student_set_model(synth.pack_blob(synth.student_spec(teacher, params)))
+        m.student_use(True)
+        _, fs, _ = m.compute(w["coords"], w["types"], w["box"])
+        expect = float(((fs - ft) ** 2).sum(1).mean().sqrt())
+        m.student_judge(20, 1e6 if keep else 1e-3, sample_side=0.0 if keep else side)
+        th = _md(m, w, 0 if keep else 20, prec)
+        st = m.stats()
+        say(f"  keep={keep}: RMSE {st['last_judge_rmse']:.9e} over {st['judge_atoms']}, expected {expect:.9e}")
+        assert abs(st["last_judge_rmse"] - expect) <= 1e-6 * expect
+        assert st["judge_atoms"] == n and st["teacher_fallbacks"] == (0 if keep else 1)
+        if not keep:
+            tol = 1e-9 if prec == "fp64" else 1e-7
+            np.testing.assert_allclose(th, want, rtol=tol, atol=tol)
