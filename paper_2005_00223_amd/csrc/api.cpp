@@ -806,7 +806,7 @@ int upload_exp(dp_ctx *c, const HostModel &m, EmbNets &en) {
       }
     }
     const bool f64 = c->precision == DP_FP64;
-    t = exp_build(nets, d.ntypes, rup(d.M1, 16), f64 ? EXP_K64 : EXP_K32, f64, f64 ? 0x1p-52 : 0x1p-25);
+    t = exp_build(nets, d.ntypes, rup(d.M1, 16), f64);
     if (!t.ok) return DP_OK;
     return f64 ? upload_exp_t<double>(c, t, en) : upload_exp_t<float>(c, t, en);
   } catch (const std::exception &) {

@@ -58,9 +58,10 @@ struct ExpTables {
   std::vector<double> C;            // [nets][P][2][EXP_KP][M1p]: C, then C'
 };
 
-// nets: ntypes^2 of them, net (t, u) at t * ntypes + u.  ext: evaluate in
-// extended precision (for double kernels).
-ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, int K, bool ext, double tol);
+// nets: ntypes^2 of them, net (t, u) at t * ntypes + u.  f64: for double kernels
+// (K = EXP_K64, interpolated in extended precision to 2^-52), else for float
+// (EXP_K32, in double to 2^-25).
+ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, bool f64);
 
 // Device tables of one set of nets (Real = double or float).
 template <typename Real>

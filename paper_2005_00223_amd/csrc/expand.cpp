@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <iterator>
 #include <thread>
 
 #include "dp_expand.h"
@@ -11,14 +12,14 @@
 namespace dpk {
 namespace {
 
-// What the interpolation in double can still tell from its rounding.
+// What the interpolation in double can still tell from its rounding: enough to
+// find the pieces, not for their coefficients in double kernels.  Many
+// neighbours of an atom share a piece, so the errors of its coefficients add up
+// (coefficients left at this accuracy beyond s = 2: NVE runs of hot water,
+// whose closest pair passes through s = 5 to 8, ended 2 to 400 times further
+// from the FP64 reference than by the layers; beyond s = 8: G there 3e-15 of
+// the largest feature off, the layers 5e-16).
 constexpr double EXP_PRE = 0x1p-48;
-// Extended precision is for s below this (pairs beyond 0.125 A): many
-// neighbours of an atom share the first pieces, and the errors of their
-// coefficients would add up.  (To 2.0 only, NVE runs of hot water, whose
-// closest pair passes through s = 5 to 8, ended 2 to 400 times further from
-// the FP64 reference than by the layers; to 8, within their spread.)
-constexpr double EXP_EXT = 8.0;
 
 // G[m], dG[m] of a net at s, forward mode through its layers.  Two outputs
 // at a time, their four sums in registers: in extended precision a sum kept
@@ -146,7 +147,9 @@ bool fit_pieces(const std::vector<ExpNetIn> &nets, int M1p, int K, double tol, s
 
 }  // namespace
 
-ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, int K, bool ext, double tol) {
+ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, bool f64) {
+  const int K = f64 ? EXP_K64 : EXP_K32;
+  const double tol = f64 ? 0x1p-52 : 0x1p-25;
   ExpTables t;
   t.K = K;
   t.M1p = M1p;
@@ -199,13 +202,12 @@ ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, int 
     }
     return true;
   };
-  if (!halve(false, ext ? std::max(tol, EXP_PRE) : tol)) return t;
-  if (ext) {
+  if (!halve(false, f64 ? EXP_PRE : tol)) return t;
+  if (f64) {
     todo.clear();
     for (auto &v : done) {
-      std::vector<Piece> rest;
-      for (auto &p : v) (p.lo < EXP_EXT ? todo : rest).push_back(std::move(p));
-      v.swap(rest);
+      std::move(v.begin(), v.end(), std::back_inserter(todo));
+      v.clear();
     }
     if (!halve(true, tol)) return t;
   }
