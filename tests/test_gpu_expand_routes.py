@@ -154,3 +154,125 @@ def test_judge_of_a_teacher_without_expansion(prec, name, side):
         if not keep:
             tol = 1e-9 if prec == "fp64" else 1e-7
             np.testing.assert_allclose(th, want, rtol=tol, atol=tol)
+
+
+# ---------------------------------------------------------------------------
+# the layers in place of the expansions: pairs beyond the range of s (closer
+# than 1/32 A for these nets), more than twelve pieces in one atom's list
+# ---------------------------------------------------------------------------
+BOX = np.array([44.0, 21.0, 21.0])
+CRYSTAL = 108
+
+
+def _frame(kind):
+    """3^3 cells of copper at one end of the box, a cluster at the other, more
+    than a cutoff away: a pair at 0.05 A (on the expansions), a pair at 0.02 A
+    (beyond them), or an atom with neighbours in 9 or
+    in 20 pieces of the double tables (none beyond them)."""
+    far, _, _ = synth.fcc_copper(3, 3.634, 0.05, seed=9)
+    rng = np.random.default_rng(4)
+    d = rng.normal(size=(40, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    r = {"in": [0.05], "pair": [0.02], "few": np.geomspace(0.25, 1.9, 10), "many": np.geomspace(0.06, 1.9, 40)}[kind]
+    c = np.array([30.0, 10.0, 10.0])
+    x = np.concatenate([far + 2.0, [c], c + d[:len(r)] * np.asarray(r)[:, None]])
+    return x, np.zeros(len(x), dtype=np.int32), BOX
+
+
+def _crystal_energies(m, kind):
+    """E_i of the crystal's atoms, whose surroundings do not depend on the
+    cluster: bit for bit the same on one route, in the last bits not on the
+    other (which is how the tests see the route)."""
+    x, t, box = _frame(kind)
+    out = m.compute(x, t, box, keep_intermediates=True)
+    e = m.intermediates(len(x), 100, 16, 512, ("atom_e",))["atom_e"].cpu().numpy()
+    return out, e[:CRYSTAL]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+def test_layers_take_over(prec):
+    spec = synth.copper_model(1)
+    m = _model(spec, prec)
+    _, e0 = _crystal_energies(m, "in")
+    for kind, layers in (("pair", True), ("few", False), ("many", True), ("in", False)):
+        if prec != "fp64" and kind == "many":
+            continue  # the float tables have fewer pieces than an atom holds
+        out, e = _crystal_energies(m, kind)
+        same = np.array_equal(e, e0)
+        say(f"[routes] {kind} {prec}: same route as the first frame {same}, E_i {np.abs(e - e0).max():.2e}")
+        assert same == (not layers)
+        assert np.abs(e - e0).max() <= {"fp64": 1e-11, "fp32": 2e-4, "fp16": 2e-4}[prec] * np.abs(e0).max()
+        x, t, box = _frame(kind)
+        if prec == "fp64":
+            _compare(out, _oracle(spec, x, t, box), prec, kind)
+        # the other entry points agree: both halves, centres first, no allocation
+        s = max(1.0, float(out[1].abs().max()))
+        tol = {"fp64": 1e-10, "fp32": 1e-6, "fp16": 1e-6}[prec]
+        m.energy(x, t, box)
+        f, v = m.energy_backward(2.0)
+        assert float((f - 2.0 * out[1]).abs().max()) <= tol * s
+        el, fl, vl = m.compute_local(x, t, box, len(x))
+        assert abs(float(el) - float(out[0])) <= tol * abs(float(out[0])) and float((fl - out[1]).abs().max()) <= tol * s
+
+
+def test_far_pair_among_the_centres_or_the_ghosts():
+    """Rank share: the far pair's atoms as centres, or as ghosts only, where no
+    centre meets it (the crystal alone has centres) and the expansions stay."""
+    spec = synth.copper_model(1)
+    m = _model(spec, "fp64")
+    x, t, box = _frame("pair")
+    r = _oracle(spec, x, t, box)
+    for n_local in (CRYSTAL, CRYSTAL + 1):
+        e, f, v = m.compute_local(x, t, box, n_local)
+        want = r["atom_e"][:n_local].sum()
+        say(f"[routes] local {n_local}: E {abs(float(e) - want):.2e}")
+        assert abs(float(e) - want) <= 1e-10 * np.abs(r["atom_e"]).sum()
+        assert np.abs(f[:CRYSTAL].cpu().numpy() - r["force"][:CRYSTAL]).max() <= 1e-9
+
+
+@pytest.mark.parametrize("thermo", [1, 4, 12])
+def test_md_passes_beyond_the_range(thermo):
+    """Two atoms fired at each other come within 0.01 A at step 7 and part
+    again.  The run restarts at that step (its later steps count twice) and
+    follows the oracle's Verlet run: 1e-7 A, and relative in the velocities
+    and energies 1e-6 (FP64 rounding amplified by the stiff encounter)."""
+    from oracle import oracle as O
+    spec = synth.copper_model(1)
+    x = np.array([[9.0, 9.0, 9.0], [9.69, 9.005, 9.0], [13.0, 10.0, 8.0]])
+    v = np.array([[0.2, 0.0, 0.0], [-0.2, 0.0, 0.0], [0.0, 0.0, 0.0]])
+    t, box, nst = np.zeros(3, dtype=np.int32), np.full(3, 21.0), 12
+    ora = O.Oracle(synth.pack_blob(spec))
+    dist = []
+    for k in range(nst + 1):
+        y = ora.verlet(x, v, t, box, [63.546], 0.25, k, every=0)[0]
+        dist.append(float(np.linalg.norm(y[0] - y[1])))
+    assert min(dist) < 0.02 and int(np.argmin(dist)) == 7 and dist[0] > 0.5 and dist[-1] > 0.3
+    xo, vo, tho = ora.verlet(x, v, t, box, [63.546], 0.25, nst, every=thermo)
+    m = _model(spec, "fp64")
+    xg, vg = torch.tensor(x, device="cuda"), torch.tensor(v, device="cuda")
+    th = m.md_run(xg, vg, t, box, [63.546], 0.25, nst, skin=1.0, thermo_every=thermo).cpu().numpy()
+    dx, dv = np.abs(xg.cpu().numpy() - xo).max(), np.abs(vg.cpu().numpy() - vo).max()
+    ev = m.stats()["evaluations"]
+    say(f"[routes] MD past {min(dist):.3f} A: x {dx:.2e}, v {dv:.2e}, {ev} evaluations")
+    assert ev == nst + -(-7 // thermo) * thermo - 7  # the steps from 7 to the next check, once more
+    assert dx <= 1e-7 and dv <= 1e-7 * max(1.0, np.abs(vo).max())
+    assert np.abs(th[:, 1:5] - tho[:, 1:5]).max() <= 1e-6 * np.abs(tho[:, 1:5]).max()
+
+
+def test_md_starts_beyond_the_range():
+    """The first frame already holds the far pair (a run of no steps too)."""
+    from oracle import oracle as O
+    spec = synth.copper_model(1)
+    x = np.array([[9.0, 9.0, 9.0], [9.015, 9.0, 9.005], [13.0, 10.0, 8.0]])
+    t, box = np.zeros(3, dtype=np.int32), np.full(3, 21.0)
+    ora = O.Oracle(synth.pack_blob(spec))
+    for nst in (0, 2):
+        xo, vo, tho = ora.verlet(x, 0 * x, t, box, [63.546], 0.01, nst, every=1)
+        m = _model(spec, "fp64")
+        xg, vg, fg = (torch.tensor(a, device="cuda") for a in (x, 0 * x, 0 * x))
+        th = m.md_run(xg, vg, t, box, [63.546], 0.01, nst, skin=1.0, thermo_every=1, forces=fg).cpu().numpy()
+        r = ora.eval(xo, t, box)
+        df = np.abs(fg.cpu().numpy() - r["force"]).max() / np.abs(r["force"]).max()
+        say(f"[routes] MD from a far pair, {nst} steps: F {df:.2e}, x {np.abs(xg.cpu().numpy() - xo).max():.2e}")
+        assert np.abs(xg.cpu().numpy() - xo).max() <= 1e-9 and df <= 1e-7
+        assert np.abs(th[:, 1:5] - tho[:, 1:5]).max() <= 1e-8 * np.abs(tho[:, 1:5]).max()
