@@ -228,12 +228,15 @@ struct EmbNets {
   double tab_shi = 0.0;             // its range of s
   bool tab_ok = false;
   bool ready = false;
-  // Chebyshev expansions of the nets, in the real type of the precision in use
-  void *d_exp = nullptr;
-  size_t exp_cf = 0, exp_cb = 0;    // element offsets of the coefficient tables
-  int exp_P = 0;
-  double exp_smax = 0.0;
-  bool exp_ok = false;
+  // Chebyshev expansions of the nets: of each precision used since the weights
+  // were loaded, so that a change of precision lays none out again
+  struct Exp {
+    void *d = nullptr;
+    size_t cf = 0, cb = 0;          // element offsets of the coefficient tables
+    int P = 0;
+    double smax = 0.0;
+    bool built = false, ok = false; // looked for; there is one
+  } exp[3];
 };
 
 struct dp_ctx {
@@ -246,9 +249,9 @@ struct dp_ctx {
   FitOffsets fo{};
   double *d_fit = nullptr;
   float *d_fit32 = nullptr;         // fitting weights rounded to FP32 (DP_MIX_FP32)
-  // FP64 / FP32 fitting weights packed as MFMA operands, in the real type of
-  // the precision in use (fused kernels)
-  void *d_fit_pack = nullptr;
+  // FP64 and FP32 fitting weights packed as MFMA operands (fused kernels), each
+  // once its precision is in use
+  void *d_fit_pack[2] = {nullptr, nullptr};
   FitPack fpk{};
   // mixed-precision fitting weights (16-bit MFMA operands + f32)
   unsigned char *d_fit_mix = nullptr;
@@ -734,32 +737,50 @@ int upload_mix(dp_ctx *c) {
   return DP_OK;
 }
 
-// Fitting weights of the fused FP64 / FP32 kernels (none: the layer GEMMs run).
-int upload_fit_pack(dp_ctx *c) {
-  if (c->d_fit_pack) (void)hipFree(c->d_fit_pack);
-  c->d_fit_pack = nullptr;
-  if (prec16(c->precision) || !fit_fused_supported(c->dims)) return DP_OK;
-  c->fpk = fit_pack_layout(c->dims);
-  if (c->precision == DP_FP64) {
-    HIPCHK(c, hipMalloc(&c->d_fit_pack, sizeof(double) * c->fpk.total));
-    launch_fit_pack<double>(c->stream, c->dims, c->fo, c->d_fit, c->fpk, (double *)c->d_fit_pack);
-  } else {
-    HIPCHK(c, hipMalloc(&c->d_fit_pack, sizeof(float) * c->fpk.total));
-    launch_fit_pack<float>(c->stream, c->dims, c->fo, c->d_fit32, c->fpk, (float *)c->d_fit_pack);
+// The tables of a precision among those kept: 0 FP64, 1 FP32, 2 FP16, -1 none.
+inline int exp_kind(int precision) {
+  return precision == DP_FP64 ? 0 : precision == DP_MIX_FP32 ? 1 : precision == DP_MIX_FP16 ? 2 : -1;
+}
+
+void drop_exp(EmbNets &en) {
+  for (auto &e : en.exp) {
+    if (e.d) (void)hipFree(e.d);
+    e = EmbNets::Exp{};
   }
+}
+
+void drop_fit_pack(dp_ctx *c) {
+  for (auto &p : c->d_fit_pack) {
+    if (p) (void)hipFree(p);
+    p = nullptr;
+  }
+}
+
+// Fitting weights of the fused FP64 / FP32 kernels for the given precision
+// (none, or no memory for them: the layer GEMMs run).
+int upload_fit_pack(dp_ctx *c, int precision) {
+  if (prec16(precision) || !fit_fused_supported(c->dims)) return DP_OK;
+  const bool f64 = precision == DP_FP64;
+  void *&pack = c->d_fit_pack[f64 ? 0 : 1];
+  if (pack) return DP_OK;
+  c->fpk = fit_pack_layout(c->dims);
+  if (hipMalloc(&pack, (f64 ? sizeof(double) : sizeof(float)) * c->fpk.total) != hipSuccess) {
+    (void)hipGetLastError();
+    pack = nullptr;
+    return DP_OK;
+  }
+  if (f64) launch_fit_pack<double>(c->stream, c->dims, c->fo, c->d_fit, c->fpk, (double *)pack);
+  else launch_fit_pack<float>(c->stream, c->dims, c->fo, c->d_fit32, c->fpk, (float *)pack);
   HIPCHK(c, hipGetLastError());
   return DP_OK;
 }
 
-// Expansions of the nets of m (dp_expand.h) for the precision in use, with
-// the weights its layer kernels hold.  Nets without one leave exp_ok false.
 template <typename Real>
-int upload_exp_t(dp_ctx *c, const ExpTables &t, EmbNets &en) {
-  const int nets = en.d.ntypes * en.d.ntypes;
-  const size_t np = (size_t)nets * t.P, blk = (size_t)EXP_KP * t.M1p;
-  en.exp_cf = np * 4;
-  en.exp_cb = en.exp_cf + np * blk;
-  std::vector<Real> h(en.exp_cb + np * 2 * blk);
+int upload_exp_t(dp_ctx *c, const ExpTables &t, int ntypes, EmbNets::Exp &e) {
+  const size_t np = (size_t)ntypes * ntypes * t.P, blk = (size_t)EXP_KP * t.M1p;
+  e.cf = np * 4;
+  e.cb = e.cf + np * blk;
+  std::vector<Real> h(e.cb + np * 2 * blk);
   for (size_t q = 0; q < np; ++q) {
     h[4 * q] = (Real)t.lo[q];
     h[4 * q + 1] = (Real)t.mid[q];
@@ -767,28 +788,34 @@ int upload_exp_t(dp_ctx *c, const ExpTables &t, EmbNets &en) {
     const double *C = t.C.data() + q * 2 * blk;
     for (size_t k = 0; k < (size_t)EXP_KP; ++k)
       for (size_t m = 0; m < (size_t)t.M1p; ++m) {
-        h[en.exp_cf + q * blk + k * t.M1p + m] = (Real)C[k * t.M1p + m];
-        h[en.exp_cb + q * 2 * blk + m * EXP_KP + k] = (Real)C[k * t.M1p + m];
-        h[en.exp_cb + (q * 2 + 1) * blk + m * EXP_KP + k] = (Real)C[blk + k * t.M1p + m];
+        h[e.cf + q * blk + k * t.M1p + m] = (Real)C[k * t.M1p + m];
+        h[e.cb + q * 2 * blk + m * EXP_KP + k] = (Real)C[k * t.M1p + m];
+        h[e.cb + (q * 2 + 1) * blk + m * EXP_KP + k] = (Real)C[blk + k * t.M1p + m];
       }
   }
-  HIPCHK(c, hipMalloc(&en.d_exp, sizeof(Real) * h.size()));
-  HIPCHK(c, hipMemcpy(en.d_exp, h.data(), sizeof(Real) * h.size(), hipMemcpyHostToDevice));
-  en.exp_P = t.P;
-  en.exp_smax = t.smax;
-  en.exp_ok = true;
+  if (e.d) (void)hipFree(e.d);
+  if (hipMalloc(&e.d, sizeof(Real) * h.size()) != hipSuccess) {
+    (void)hipGetLastError();
+    e.d = nullptr;
+    return DP_OK;  // no memory for them: the layer kernels evaluate the nets
+  }
+  HIPCHK(c, hipMemcpy(e.d, h.data(), sizeof(Real) * h.size(), hipMemcpyHostToDevice));
+  e.P = t.P;
+  e.smax = t.smax;
+  e.built = e.ok = true;
   return DP_OK;
 }
 
-int upload_exp(dp_ctx *c, const HostModel &m, EmbNets &en) {
-  if (en.d_exp) (void)hipFree(en.d_exp);
-  en.d_exp = nullptr;
-  en.exp_ok = false;
+// Expansions of the nets of m (dp_expand.h) for the given precision, with the
+// weights its layer kernels hold.  Nets without one leave ok false.
+int upload_exp(dp_ctx *c, const HostModel &m, EmbNets &en, int precision) {
+  const int kind = exp_kind(precision);
   // BF16, wide nets and the 16-bit student nets keep their layer kernels:
   // their results carry those kernels' own rounding (5e-5 and 1e-4 of the
   // forces on copper), and callers' trajectories with it
   const Dims &d = en.d;
-  if (c->precision == DP_MIX_BF16 || (c->precision == DP_MIX_FP16 && (en.wide || &en == &c->en[1]))) return DP_OK;
+  if (kind < 0 || en.exp[kind].built) return DP_OK;
+  if (precision == DP_MIX_FP16 && (mix_shape_id(d) < 0 || &en == &c->en[1])) return DP_OK;
   ExpTables t;
   try {
     std::vector<ExpNetIn> nets((size_t)d.ntypes * d.ntypes);
@@ -800,15 +827,19 @@ int upload_exp(dp_ctx *c, const HostModel &m, EmbNets &en) {
       for (int l = 0; l < d.n_emb; ++l) {
         n.W[l] = m.eW[(size_t)k * d.n_emb + l];
         n.b[l] = m.eb[(size_t)k * d.n_emb + l];
-        if (c->precision == DP_FP64) continue;
+        if (precision == DP_FP64) continue;
         for (auto &v : n.b[l]) v = (float)v;
-        for (auto &v : n.W[l]) v = c->precision == DP_MIX_FP16 && l > 0 ? st_round16((float)v, 0) : (double)(float)v;
+        for (auto &v : n.W[l]) v = precision == DP_MIX_FP16 && l > 0 ? st_round16((float)v, 0) : (double)(float)v;
       }
     }
-    const bool f64 = c->precision == DP_FP64;
+    const bool f64 = precision == DP_FP64;
     t = exp_build(nets, d.ntypes, rup(d.M1, 16), f64);
-    if (!t.ok) return DP_OK;
-    return f64 ? upload_exp_t<double>(c, t, en) : upload_exp_t<float>(c, t, en);
+    EmbNets::Exp &e = en.exp[kind];
+    if (!t.ok) {
+      e.built = true;
+      return DP_OK;
+    }
+    return f64 ? upload_exp_t<double>(c, t, d.ntypes, e) : upload_exp_t<float>(c, t, d.ntypes, e);
   } catch (const std::exception &) {
     return DP_OK;  // out of host memory: the layer kernels evaluate the nets
   }
@@ -1007,10 +1038,13 @@ int64_t eval_rows(const dp_ctx *c, int64_t n) {
 }
 
 // Whether an evaluation of the active nets runs on their expansions.
-inline bool use_exp(const dp_ctx *c) { return c->en[c->active].exp_ok && !c->exp_off && c->ws.exp_hm; }
+inline bool use_exp(const dp_ctx *c) {
+  const int kind = exp_kind(c->precision);
+  return kind >= 0 && c->en[c->active].exp[kind].ok && !c->exp_off && c->ws.exp_hm;
+}
 
 // ... and its fitting net in the fused kernels (no D, dE/dT in place of dE/dD)
-inline bool use_fused(const dp_ctx *c) { return c->exp_now && c->d_fit_pack; }
+inline bool use_fused(const dp_ctx *c) { return c->exp_now && !prec16(c->precision) && c->d_fit_pack[c->precision == DP_FP64 ? 0 : 1]; }
 
 template <typename Real>
 FitFusedArgs<Real> fused_args(dp_ctx *c, int64_t rows) {
@@ -1020,7 +1054,7 @@ FitFusedArgs<Real> fused_args(dp_ctx *c, int64_t rows) {
   a.fo = c->fo;
   a.fwt = sizeof(Real) == 8 ? (const Real *)c->d_fit : (const Real *)c->d_fit32;
   a.pk = c->fpk;
-  a.pack = (const Real *)c->d_fit_pack;
+  a.pack = (const Real *)c->d_fit_pack[sizeof(Real) == 8 ? 0 : 1];
   a.type_start = c->ov_type_start ? c->ov_type_start : w.type_start;
   a.atom_of_pos = c->ov_atom_of_pos ? c->ov_atom_of_pos : w.atom_of_pos;
   a.rows = rows;
@@ -1042,14 +1076,15 @@ template <typename Real>
 ExpArgs<Real> exp_args(dp_ctx *c, int64_t rows, double *F) {
   Workspace &w = c->ws;
   const EmbNets &en = c->en[c->active];
+  const EmbNets::Exp &e = en.exp[exp_kind(c->precision)];
   ExpArgs<Real> a{};
   a.d = en.d;
-  a.tab.P = en.exp_P;
+  a.tab.P = e.P;
   a.tab.M1p = rup(en.d.M1, 16);
-  a.tab.smax = (Real)en.exp_smax;
-  a.tab.piece = (const Real *)en.d_exp;
-  a.tab.Cf = (const Real *)en.d_exp + en.exp_cf;
-  a.tab.Cb = (const Real *)en.d_exp + en.exp_cb;
+  a.tab.smax = (Real)e.smax;
+  a.tab.piece = (const Real *)e.d;
+  a.tab.Cf = (const Real *)e.d + e.cf;
+  a.tab.Cb = (const Real *)e.d + e.cb;
   a.seg = w.seg;
   a.atom_of_pos = c->ov_atom_of_pos ? c->ov_atom_of_pos : w.atom_of_pos;
   a.rows = rows;
@@ -1744,13 +1779,14 @@ int install_student(dp_ctx *c, HostModel &&m) {
   c->en[1].ready = false;
   c->fwd_ready = false;  // a pending backward would meet other nets
   c->shm = std::move(m);
+  drop_exp(c->en[1]);
   int rc = upload_emb(c, c->shm, c->en[1]);
   if (rc) return rc;
   if (prec16(c->precision)) {
     rc = upload_emb_mix(c, c->shm, c->en[1]);
     if (rc) return rc;
   }
-  rc = upload_exp(c, c->shm, c->en[1]);
+  rc = upload_exp(c, c->shm, c->en[1], c->precision);
   if (rc) return rc;
   c->en[1].ready = true;
   return DP_OK;
@@ -1867,14 +1903,14 @@ void dp_destroy(dp_ctx *c) {
     if (en.d_mix) (void)hipFree(en.d_mix);
     if (en.d_tab) (void)hipFree(en.d_tab);
     if (en.d_wide) (void)hipFree(en.d_wide);
-    if (en.d_exp) (void)hipFree(en.d_exp);
+    drop_exp(en);
   }
   free_wide(c);
   free_student(c);
   if (c->d_fit) (void)hipFree(c->d_fit);
   if (c->d_fit32) (void)hipFree(c->d_fit32);
   if (c->d_fit_mix) (void)hipFree(c->d_fit_mix);
-  if (c->d_fit_pack) (void)hipFree(c->d_fit_pack);
+  drop_fit_pack(c);
   if (c->h_status) (void)hipHostFree(c->h_status);
   for (auto &e : c->ev)
     if (e) (void)hipEventDestroy(e);
@@ -1899,6 +1935,8 @@ int dp_set_model(dp_ctx *c, const void *blob, size_t nbytes, int precision) {
   c->active = 0;
   c->en[1].ready = false;
   if (c->st) c->st->have_params = false;
+  for (auto &en : c->en) drop_exp(en);
+  drop_fit_pack(c);
   int rc = upload_model(c);
   if (rc) return rc;
   const char *why = nullptr;
@@ -1908,9 +1946,9 @@ int dp_set_model(dp_ctx *c, const void *blob, size_t nbytes, int precision) {
     rc = upload_mix(c);
     if (rc) return rc;
   }
-  rc = upload_exp(c, c->hm, c->en[0]);
+  rc = upload_exp(c, c->hm, c->en[0], precision);
   if (rc) return rc;
-  rc = upload_fit_pack(c);
+  rc = upload_fit_pack(c, precision);
   if (rc) return rc;
   c->has_model = true;
   return DP_OK;
@@ -1922,21 +1960,19 @@ int dp_set_precision(dp_ctx *c, int precision) {
   if (!prec_ok(precision)) return fail(c, DP_E_ARG, "unsupported precision policy");
   const char *why = nullptr;
   if (!prec16(precision) && !f64_emb_ok(c->dims, &why)) return fail(c, DP_E_MODEL, why);
-  const int old = c->precision;
+  HIPCHK(c, hipSetDevice(c->device));
   c->fwd_ready = false;  // the forward's buffers belong to the old precision
+  // first what is kept beside the old precision's, so that a failure leaves that as it is
+  int rc = upload_exp(c, c->hm, c->en[0], precision);
+  if (!rc) rc = upload_fit_pack(c, precision);
+  if (!rc && c->en[1].ready) rc = upload_exp(c, c->shm, c->en[1], precision);
+  if (rc) return rc;
+  const int old = c->precision;
   c->precision = precision;
   if (prec16(precision)) {
-    int rc = upload_mix(c);
-    if (rc) {
-      c->precision = old;
-      return rc;
-    }
+    rc = upload_mix(c);
+    if (rc) c->precision = old;
   }
-  if (precision == old) return DP_OK;
-  c->en[0].exp_ok = c->en[1].exp_ok = false;  // the old precision's tables
-  int rc = upload_exp(c, c->hm, c->en[0]);
-  if (!rc) rc = upload_fit_pack(c);
-  if (!rc && c->en[1].ready) rc = upload_exp(c, c->shm, c->en[1]);
   return rc;
 }
 

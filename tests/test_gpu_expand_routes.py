@@ -276,3 +276,53 @@ def test_md_starts_beyond_the_range():
         say(f"[routes] MD from a far pair, {nst} steps: F {df:.2e}, x {np.abs(xg.cpu().numpy() - xo).max():.2e}")
         assert np.abs(xg.cpu().numpy() - xo).max() <= 1e-9 and df <= 1e-7
         assert np.abs(th[:, 1:5] - tho[:, 1:5]).max() <= 1e-8 * np.abs(tho[:, 1:5]).max()
+
+
+# ---------------------------------------------------------------------------
+# change of precision
+# ---------------------------------------------------------------------------
+def test_precision_changes_with_a_student():
+    """Through every precision and back, teacher and student: energies bit for
+    bit those of a context that was loaded in that precision, forces but for
+    the atomics' order."""
+    w = synth.workload("water192")
+    spec = w["spec"]
+    sblob = synth.pack_blob(synth.student_spec(spec, synth.random_student_params(spec, 12)))
+
+    def both(m):
+        out = []
+        for use in (False, True):
+            m.student_use(use)
+            e, f, _ = m.compute(w["coords"], w["types"], w["box"])
+            out.append((float(e), f.cpu().numpy()))
+        return out
+
+    want = {}
+    for prec in ("fp64", "fp32", "fp16", "bf16"):
+        fresh = _model(spec, prec)
+        fresh.student_set_model(sblob)
+        fresh.student_table(False)
+        want[prec] = both(fresh)
+    m = _model(spec, "fp64")
+    m.student_set_model(sblob)
+    m.student_table(False)
+    for prec in ("fp32", "fp64", "bf16", "fp64", "fp16", "fp32", "bf16", "fp16", "fp64"):
+        m.set_precision(prec)
+        for (e, f), (e0, f0) in zip(both(m), want[prec]):
+            say(f"[routes] to {prec}: E {abs(e - e0):.1e}, F {np.abs(f - f0).max():.1e}")
+            assert e == e0 and np.abs(f - f0).max() <= 1e-11
+
+
+def test_precision_change_lays_nothing_out_twice():
+    """FP64 to FP32 and back once both have been used: the tables are there.
+    (Laying the water nets' out takes 20 ms and more.)"""
+    import time
+    m = _model(synth.workload("water192")["spec"], "fp64")
+    m.set_precision("fp32")
+    took = []
+    for k in range(10):
+        t0 = time.perf_counter()
+        m.set_precision("fp32" if k & 1 else "fp64")
+        took.append(time.perf_counter() - t0)
+    say(f"[routes] change of precision {min(took) * 1e3:.3f} .. {max(took) * 1e3:.3f} ms")
+    assert sorted(took)[5] <= 2e-3
