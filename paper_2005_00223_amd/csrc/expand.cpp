@@ -4,7 +4,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
-#include <iterator>
 #include <thread>
 
 #include "dp_expand.h"
@@ -21,47 +20,135 @@ namespace {
 // the largest feature off, the layers 5e-16).
 constexpr double EXP_PRE = 0x1p-48;
 
-// G[m], dG[m] of a net at s, forward mode through its layers.  Two outputs
-// at a time, their four sums in registers: in extended precision a sum kept
-// in memory costs a 10-byte store and load per term.
-template <typename F>
-void net_eval(const ExpNetIn &n, F s, std::vector<F> &h, std::vector<F> &hd, std::vector<F> &z, std::vector<F> &zd) {
-  h.assign(1, s);
-  hd.assign(1, F(1));
-  for (int l = 0; l < n.n_layers; ++l) {
-    const int in = n.w[l], out = n.w[l + 1];
-    z.resize(out);
-    zd.resize(out);
-    const double *W = n.W[l].data();
-    for (int o = 0; o < out; o += 2) {
-      const int o1 = o + 1 < out ? o + 1 : o;
-      F a = (F)n.b[l][o], b = (F)n.b[l][o1], ad = 0, bd = 0;
-      for (int i = 0; i < in; ++i) {
-        const F x = h[i], xd = hd[i], wa = (F)W[(size_t)i * out + o], wb = (F)W[(size_t)i * out + o1];
-        a += x * wa;
-        ad += xd * wa;
-        b += x * wb;
-        bd += xd * wb;
-      }
-      z[o] = a;
-      zd[o] = ad;
-      z[o1] = b;
-      zd[o1] = bd;
+// A net's weights with the inputs of an output contiguous.
+struct NetT {
+  const ExpNetIn *n;
+  std::vector<double> W[MAXL];
+  explicit NetT(const ExpNetIn &net) : n(&net) {
+    for (int l = 0; l < net.n_layers; ++l) {
+      const size_t in = net.w[l], out = net.w[l + 1];
+      W[l].resize(in * out);
+      for (size_t i = 0; i < in; ++i)
+        for (size_t o = 0; o < out; ++o) W[l][o * in + i] = net.W[l][i * out + o];
     }
-    if (!(n.lin && l + 1 == n.n_layers))
-      for (int o = 0; o < out; ++o) {
-        const F t = std::tanh(z[o]);
-        z[o] = t;
-        zd[o] *= F(1) - t * t;
+  }
+  // a point's time in ns: products (value and tangent), then tanh
+  double ns(bool extended) const {
+    double s = 0.0;
+    for (int l = 0; l < n->n_layers; ++l)
+      s += 2.0 * (double)W[l].size() * (extended ? 2.0 : 0.3) + n->w[l + 1] * (extended ? 100.0 : 30.0);
+    return s;
+  }
+};
+
+template <typename F>
+struct Buffers {
+  std::vector<F> h, hd, z, zd;
+};
+
+// The layers' products for J points at once (feature-major, [feature][J]): the
+// sums of one output's J points stay in registers.
+template <int J>
+void products(const double *__restrict__ w, double b, int in, const double *__restrict__ h, double *__restrict__ z) {
+  double a[J];
+  for (int j = 0; j < J; ++j) a[j] = b;
+  for (int i = 0; i < in; ++i)
+    for (int j = 0; j < J; ++j) a[j] += w[i] * h[(size_t)i * J + j];
+  for (int j = 0; j < J; ++j) z[j] = a[j];
+}
+
+// Two outputs of one point, value and tangent: in extended precision a sum
+// kept in memory costs a 10-byte store and load per term, and four fit the
+// register stack.
+inline void products2(const double *__restrict__ wa, const double *__restrict__ wb, int in,
+                      const long double *__restrict__ h, const long double *__restrict__ hd, long double (&s)[4]) {
+  long double a = s[0], ad = s[1], b = s[2], bd = s[3];
+  for (int i = 0; i < in; ++i) {
+    const long double x = h[i], xd = hd[i];
+    a += x * wa[i];
+    ad += xd * wa[i];
+    b += x * wb[i];
+    bd += xd * wb[i];
+  }
+  s[0] = a;
+  s[1] = ad;
+  s[2] = b;
+  s[3] = bd;
+}
+
+// tanh and the skips of layer l over J points, z and zd in place
+template <typename F>
+void layer_end(const ExpNetIn &n, int l, int J, Buffers<F> &u) {
+  const int in = n.w[l], out = n.w[l + 1];
+  if (!(n.lin && l + 1 == n.n_layers))
+    for (int o = 0; o < out; ++o)
+      for (int j = 0; j < J; ++j) {
+        const size_t e = (size_t)o * J + j;
+        const F t = std::tanh(u.z[e]);
+        u.z[e] = t;
+        u.zd[e] *= F(1) - t * t;
         if (out == in || out == 2 * in) {
-          const int k = o >= in ? o - in : o;
-          z[o] += h[k];
-          zd[o] += hd[k];
+          const size_t k = (size_t)(o >= in ? o - in : o) * J + j;
+          u.z[e] += u.h[k];
+          u.zd[e] += u.hd[k];
         }
       }
-    h.swap(z);
-    hd.swap(zd);
+  u.h.swap(u.z);
+  u.hd.swap(u.zd);
+}
+
+// u.h, u.hd = G[m][J], dG[m][J] of a net at s[J], forward mode through its layers
+template <int J>
+void net_eval(const NetT &t, const double *s, Buffers<double> &u) {
+  const ExpNetIn &n = *t.n;
+  u.h.assign(s, s + J);
+  u.hd.assign(J, 1.0);
+  for (int l = 0; l < n.n_layers; ++l) {
+    const int in = n.w[l], out = n.w[l + 1];
+    u.z.resize((size_t)out * J);
+    u.zd.resize((size_t)out * J);
+    for (int o = 0; o < out; ++o) {
+      const double *w = t.W[l].data() + (size_t)o * in;
+      products<J>(w, n.b[l][o], in, u.h.data(), u.z.data() + (size_t)o * J);
+      products<J>(w, 0.0, in, u.hd.data(), u.zd.data() + (size_t)o * J);
+    }
+    layer_end(n, l, J, u);
   }
+}
+
+template <int J>
+void net_eval(const NetT &t, const long double *s, Buffers<long double> &u) {
+  const ExpNetIn &n = *t.n;
+  std::vector<long double> G, D;
+  for (int j = 0; j < J; ++j) {
+    u.h.assign(1, s[j]);
+    u.hd.assign(1, 1.0L);
+    for (int l = 0; l < n.n_layers; ++l) {
+      const int in = n.w[l], out = n.w[l + 1];
+      u.z.resize(out);
+      u.zd.resize(out);
+      for (int o = 0; o < out; o += 2) {
+        const int o1 = o + 1 < out ? o + 1 : o;
+        const double *w = t.W[l].data();
+        long double a[4] = {n.b[l][o], 0.0L, n.b[l][o1], 0.0L};
+        products2(w + (size_t)o * in, w + (size_t)o1 * in, in, u.h.data(), u.hd.data(), a);
+        u.z[o] = a[0];
+        u.zd[o] = a[1];
+        u.z[o1] = a[2];
+        u.zd[o1] = a[3];
+      }
+      layer_end(n, l, 1, u);
+    }
+    const size_t m1 = u.h.size();
+    G.resize(m1 * J);
+    D.resize(m1 * J);
+    for (size_t m = 0; m < m1; ++m) {
+      G[m * J + j] = u.h[m];
+      D[m * J + j] = u.hd[m];
+    }
+  }
+  u.h.swap(G);
+  u.hd.swap(D);
 }
 
 struct Piece {
@@ -96,53 +183,45 @@ bool parallel_for(size_t n, size_t nthreads, Fn f) {
   return good;
 }
 
-// Interpolates the pieces' nets in the real type F and sets ok where the
-// last two coefficients of every feature are within tol.
-template <typename F>
-bool fit_pieces(const std::vector<ExpNetIn> &nets, int M1p, int K, double tol, std::vector<Piece> &pieces) {
+// Interpolates the pieces' nets in the real type F at J nodes and sets ok where
+// the last two coefficients of every feature are within tol.
+template <typename F, int J>
+bool fit_pieces(const std::vector<NetT> &nets, int M1p, double tol, std::vector<Piece> &pieces) {
   const F pi = (F)3.14159265358979323846264338327950288L;
-  const int M1 = pieces.empty() ? 0 : nets[0].w[nets[0].n_layers];
-  const size_t blk = (size_t)K * M1;
-  // threads only where the work outweighs starting them
-  const size_t nth = sizeof(F) > sizeof(double) ? 4 : 1;
-  std::vector<F> val(pieces.size() * 2 * blk), ct((size_t)K * K);
-  for (int k = 0; k < K; ++k)
-    for (int j = 0; j < K; ++j)
-      ct[k * K + j] = std::cos(pi * (F)k * ((F)j + F(0.5)) / K) * (k == 0 ? F(1) : F(2)) / K;
-  bool good = parallel_for(pieces.size() * K, nth, [&](size_t q) {
-    const Piece &p = pieces[q / K];
-    const int j = (int)(q % K);
-    std::vector<F> h, hd, z, zd;
-    net_eval<F>(nets[p.net], ((F)p.lo + (F)p.hi) / 2 + ((F)p.hi - (F)p.lo) / 2 * std::cos(pi * ((F)j + F(0.5)) / K), h,
-                hd, z, zd);
-    std::copy(h.begin(), h.end(), val.begin() + q / K * 2 * blk + (size_t)j * M1);
-    std::copy(hd.begin(), hd.end(), val.begin() + (q / K * 2 + 1) * blk + (size_t)j * M1);
-  });
-  good = good && parallel_for(pieces.size(), nth, [&](size_t q) {
+  F ct[J][J], node[J];
+  for (int k = 0; k < J; ++k) {
+    node[k] = std::cos(pi * ((F)k + F(0.5)) / J);
+    for (int j = 0; j < J; ++j) ct[k][j] = std::cos(pi * (F)k * ((F)j + F(0.5)) / J) * (k == 0 ? F(1) : F(2)) / J;
+  }
+  // as many threads as have 0.3 ms of work each: starting one takes some 0.03 ms
+  double ns = 0.0;
+  for (auto &p : pieces) ns += nets[p.net].ns(sizeof(F) > sizeof(double)) * J;
+  const size_t nth = (size_t)std::min(8.0, 1.0 + ns / 3e5);
+  return parallel_for(pieces.size(), nth, [&](size_t q) {
     Piece &p = pieces[q];
+    Buffers<F> u;
+    F s[J];
+    for (int j = 0; j < J; ++j) s[j] = ((F)p.lo + (F)p.hi) / 2 + ((F)p.hi - (F)p.lo) / 2 * node[j];
+    net_eval<J>(nets[p.net], s, u);
     p.C.assign((size_t)2 * EXP_KP * M1p, 0.0);
     p.ok = true;
-    std::vector<F> acc(M1);
     for (int w = 0; w < 2; ++w) {
-      const F *g = val.data() + (q * 2 + w) * blk;
+      const std::vector<F> &g = w ? u.hd : u.h;
       F big = 0, tail = 0;
-      for (size_t e = 0; e < blk; ++e) {
-        big = std::max(big, std::fabs(g[e]));
-        if (!std::isfinite((double)g[e])) p.ok = false;
+      for (const F &v : g) {
+        big = std::max(big, std::fabs(v));
+        if (!std::isfinite((double)v)) p.ok = false;
       }
-      for (int k = 0; k < K; ++k) {
-        std::fill(acc.begin(), acc.end(), F(0));
-        for (int j = 0; j < K; ++j)
-          for (int m = 0; m < M1; ++m) acc[m] += ct[k * K + j] * g[(size_t)j * M1 + m];
-        for (int m = 0; m < M1; ++m) {
-          p.C[(size_t)(w * EXP_KP + k) * M1p + m] = (double)acc[m];
-          if (k >= K - 2) tail = std::max(tail, std::fabs(acc[m]));
+      for (size_t m = 0; m < g.size() / J; ++m)
+        for (int k = 0; k < J; ++k) {
+          F a = 0;
+          for (int j = 0; j < J; ++j) a += ct[k][j] * g[m * J + j];
+          p.C[(size_t)(w * EXP_KP + k) * M1p + m] = (double)a;
+          if (k >= J - 2) tail = std::max(tail, std::fabs(a));
         }
-      }
       if (!(tail <= (F)tol * big)) p.ok = false;
     }
   });
-  return good;
 }
 
 }  // namespace
@@ -154,24 +233,32 @@ ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, bool
   t.K = K;
   t.M1p = M1p;
   const int nn = (int)nets.size();
+  std::vector<NetT> nt(nets.begin(), nets.end());
   const int pmax = std::min(EXP_PMAX, EXP_BITS / ntypes);
   std::vector<std::vector<Piece>> done(nn);
   std::vector<Piece> todo;
-  for (int k = 0; k < nn; ++k)
-    for (double hi = 2.0; hi <= EXP_SMAX; hi *= 2.0) {
-      Piece p;
-      p.net = k;
-      p.lo = hi > 2.0 ? 0.5 * hi : 0.0;
-      p.hi = hi;
-      todo.push_back(p);
+  // Pieces below s = 1 of a centre type's nets, so far or at least: most of an
+  // atom's neighbours lie beyond 1 A, and nets so rough that they lie in more
+  // pieces than the atom's rows hold have no expansion.
+  auto rough = [&]() {
+    for (int c = 0; c < ntypes; ++c) {
+      int bulk = 0;
+      for (int u = 0; u < ntypes; ++u) {
+        for (auto &p : done[c * ntypes + u]) bulk += p.lo < 1.0 ? 1 : 0;
+        for (auto &p : todo) bulk += p.net == c * ntypes + u && p.lo < 1.0 ? 1 : 0;
+      }
+      if (bulk > EXP_SEG - 4) return true;
     }
+    return false;
+  };
   // Halve until every interval is within tol; intervals past a net's pmax-th
-  // from the left can never be used.  For the extended precision, double
-  // finds the intervals first, to above its own rounding.
+  // from the left can never be used.  False: no expansion.
   auto halve = [&](bool extended, double tl) {
     for (int level = 0; level < 10 && !todo.empty(); ++level) {
-      if (!(extended ? fit_pieces<long double>(nets, M1p, K, tl, todo) : fit_pieces<double>(nets, M1p, K, tl, todo)))
-        return false;
+      const bool good = extended ? fit_pieces<long double, EXP_K64>(nt, M1p, tl, todo)
+                        : f64    ? fit_pieces<double, EXP_K64>(nt, M1p, tl, todo)
+                                 : fit_pieces<double, EXP_K32>(nt, M1p, tl, todo);
+      if (!good) return false;
       std::vector<Piece> rest;
       for (auto &p : todo) {
         if (p.ok) {
@@ -199,15 +286,31 @@ ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, bool
         rest.erase(std::remove_if(rest.begin(), rest.end(), past), rest.end());
       }
       todo.swap(rest);
+      if (rough()) return false;
     }
     return true;
   };
-  if (!halve(false, f64 ? EXP_PRE : tol)) return t;
-  if (f64) {
+  // For the extended precision, double finds the intervals first, to above its
+  // own rounding; [0, 2] before the rest, which says of rough nets that they
+  // are (four and more types in double: 60 ms and more of work for nothing).
+  for (int far = 0; far < 2; ++far) {
+    todo.clear();
+    for (int k = 0; k < nn; ++k)
+      for (double hi = far ? 2.0 * EXP_SMIN : EXP_SMIN; hi <= (far ? EXP_SMAX : EXP_SMIN); hi *= 2.0) {
+        Piece p;
+        p.net = k;
+        p.lo = far ? 0.5 * hi : 0.0;
+        p.hi = hi;
+        todo.push_back(p);
+      }
+    if (!halve(false, f64 ? EXP_PRE : tol)) return t;
+  }
+  for (int far = 0; f64 && far < 2; ++far) {
     todo.clear();
     for (auto &v : done) {
-      std::move(v.begin(), v.end(), std::back_inserter(todo));
-      v.clear();
+      std::vector<Piece> rest;
+      for (auto &p : v) ((p.lo >= EXP_SMIN) == (far != 0) ? todo : rest).push_back(std::move(p));
+      v.swap(rest);
     }
     if (!halve(true, tol)) return t;
   }
@@ -224,14 +327,8 @@ ExpTables exp_build(const std::vector<ExpNetIn> &nets, int ntypes, int M1p, bool
     t.P = std::max(t.P, (int)q);
   }
   if (smax < EXP_SMIN) return t;
-  // rough nets: an atom's neighbours, most of them beyond 1 A, would lie in
-  // more pieces than its rows hold
-  for (int c = 0; c < ntypes; ++c) {
-    int bulk = 0;
-    for (int u = 0; u < ntypes; ++u)
-      for (auto &p : done[c * ntypes + u]) bulk += p.lo < 1.0 ? 1 : 0;
-    if (bulk > EXP_SEG - 4) return t;
-  }
+  todo.clear();
+  if (rough()) return t;
   t.smax = smax;
   const size_t row = (size_t)2 * EXP_KP * M1p;
   t.lo.assign((size_t)nn * t.P, HUGE_VAL);

@@ -108,3 +108,26 @@ def test_tables_against_the_nets(lib, name, f64):
                 e = [float(np.abs(g - w).max() / np.abs(w).max()) for g, w in zip(got, want)]
                 print(f"{name} ({t},{u}) s {a:g}..{b:g}: G {e[0]:.1e}, dG {e[1]:.1e}")
                 assert max(e) <= bar, (t, u, a, b, e)
+
+
+def _steeper(spec, f):
+    for row in spec.emb_W:
+        for W in row:
+            W[0] = W[0] * f
+    return spec
+
+
+# model, has a double table, has a float table: nets that put an atom's ordinary
+# neighbours (beyond 1 A) in more than eight pieces have none
+RANGE = [(lambda: synth.random_model(3, 6.0, 2.0, (20,) * 3, seed=5), True, True),
+         (lambda: synth.random_model(4, 6.0, 2.0, (20,) * 4, seed=5), False, True),
+         (lambda: synth.random_model(8, 6.0, 2.0, (20,) * 8, seed=5), False, False),
+         (lambda: _steeper(synth.copper_model(1), 4.0), False, True),
+         (lambda: _steeper(synth.copper_model(1), 24.0), False, False)]
+
+
+@pytest.mark.parametrize("which", range(len(RANGE)))
+def test_which_nets_have_tables(lib, which):
+    make, f64, f32 = RANGE[which]
+    assert (_tables(lib, make(), True) is not None) == f64
+    assert (_tables(lib, make(), False) is not None) == f32
