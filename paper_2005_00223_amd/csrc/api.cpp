@@ -193,6 +193,7 @@ struct Workspace {
   void *exp_hm = nullptr;
   int seg = 0;
   bool env_ok = false;  // the environment rows are those of the current lists
+  bool exp_none = false; // laid out without exp_hm: no device memory for it
   int prec = -1;  // precision the buffers were laid out for
   DevStatus *status;
 };
@@ -459,25 +460,39 @@ size_t ws_carve(const dp_ctx *c, Workspace &w, int64_t nn, int64_t nc, int cc, b
   return off;
 }
 
+// The tables of a precision among those kept: 0 FP64, 1 FP32, 2 FP16, -1 none.
+inline int exp_kind(int precision) {
+  return precision == DP_FP64 ? 0 : precision == DP_MIX_FP32 ? 1 : precision == DP_MIX_FP16 ? 2 : -1;
+}
+
+// Whether an evaluation of some nets in the precision in use runs on expansions.
+bool wants_exp(const dp_ctx *c) {
+  const int kind = exp_kind(c->precision);
+  return kind >= 0 && (c->en[0].exp[kind].ok || (c->en[1].ready && c->en[1].exp[kind].ok));
+}
+
 // Make the workspace hold n atoms, ncell cells and cand_cap candidates per
 // atom.  Normally one allocation, grown by a quarter beyond the need; in
 // the no-allocation entry point the block is the device's static scratch
 // array instead, laid out for exactly this call (an error if too small).
+// The expansions' buffers (up to 12 KB an atom) are part of it where some nets
+// use them and there is memory for them; without them the layers are evaluated.
 int ensure_ws(dp_ctx *c, int64_t n, int64_t ncell, int cand_cap) {
   Workspace &w = c->ws;
   const bool need_nd = c->keep;
-  if (n <= w.n_cap && ncell <= w.ncell_cap && cand_cap <= w.cand_cap && (!need_nd || w.nd) &&
-      w.prec == c->precision)
-    return DP_OK;
+  const bool holds = n <= w.n_cap && ncell <= w.ncell_cap && cand_cap <= w.cand_cap && (!need_nd || w.nd) &&
+                     w.prec == c->precision;
+  bool exp = wants_exp(c);
   if (c->noalloc) {
+    // whether this call's system has them beside the rest, whatever the last one had
     Workspace nw{};
+    exp = exp && ws_carve(c, nw, n, ncell, cand_cap, need_nd, nullptr, true) <= NOALLOC_SCRATCH_BYTES;
+    if (holds && (!exp || w.exp_hm)) return DP_OK;
     const size_t need = ws_carve(c, nw, n, ncell, cand_cap, need_nd, nullptr, false);
     if (need > NOALLOC_SCRATCH_BYTES)
       return fail(c, DP_E_CAP, "dp_compute_noalloc: this system needs a workspace of " + std::to_string(need) +
                                    " bytes, more than the " + std::to_string(NOALLOC_SCRATCH_BYTES) +
                                    "-byte static scratch holds (use dp_compute)");
-    // with the expansions' buffers where they fit beside the rest
-    const bool exp = ws_carve(c, nw, n, ncell, cand_cap, need_nd, nullptr, true) <= NOALLOC_SCRATCH_BYTES;
     nw = Workspace{};
     nw.owned = false;
     ws_carve(c, nw, n, ncell, cand_cap, need_nd, (char *)c->scratch, exp);
@@ -485,23 +500,28 @@ int ensure_ws(dp_ctx *c, int64_t n, int64_t ncell, int cand_cap) {
     c->cgrid_ok = false;
     return DP_OK;
   }
-  int64_t nn = std::max<int64_t>(n, w.n_cap > 0 ? (w.n_cap * 5) / 4 : n);
+  if (holds && (!exp || w.exp_hm || w.exp_none)) return DP_OK;
+  int64_t nn = n <= w.n_cap ? w.n_cap : std::max<int64_t>(n, w.n_cap > 0 ? (w.n_cap * 5) / 4 : n);
   nn = std::max<int64_t>(nn, 1);
   int64_t nc = std::max<int64_t>(ncell, w.ncell_cap);
   int cc = std::max(cand_cap, w.cand_cap);
   bool nd = need_nd || w.nd;
   free_ws(w);
-  Workspace nw{};
-  const size_t off = ws_carve(c, nw, nn, nc, cc, nd, nullptr, true);
-  void *base = nullptr;
-  if (hipMalloc(&base, off) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(c, DP_E_OOM, "workspace allocation of " + std::to_string(off) + " bytes failed");
+  for (;; exp = false) {
+    Workspace nw{};
+    const size_t off = ws_carve(c, nw, nn, nc, cc, nd, nullptr, exp);
+    void *base = nullptr;
+    if (hipMalloc(&base, off) != hipSuccess) {
+      (void)hipGetLastError();
+      if (exp) continue;
+      return fail(c, DP_E_OOM, "workspace allocation of " + std::to_string(off) + " bytes failed");
+    }
+    ws_carve(c, nw, nn, nc, cc, nd, (char *)base, exp);
+    nw.exp_none = !exp && wants_exp(c);
+    w = nw;
+    c->cgrid_ok = false;
+    return DP_OK;
   }
-  ws_carve(c, nw, nn, nc, cc, nd, (char *)base, true);
-  w = nw;
-  c->cgrid_ok = false;
-  return DP_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -735,11 +755,6 @@ int upload_mix(dp_ctx *c) {
   c->fmo = fo;
   c->n16 = n16;
   return DP_OK;
-}
-
-// The tables of a precision among those kept: 0 FP64, 1 FP32, 2 FP16, -1 none.
-inline int exp_kind(int precision) {
-  return precision == DP_FP64 ? 0 : precision == DP_MIX_FP32 ? 1 : precision == DP_MIX_FP16 ? 2 : -1;
 }
 
 void drop_exp(EmbNets &en) {

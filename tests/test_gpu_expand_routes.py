@@ -326,3 +326,63 @@ def test_precision_change_lays_nothing_out_twice():
         took.append(time.perf_counter() - t0)
     say(f"[routes] change of precision {min(took) * 1e3:.3f} .. {max(took) * 1e3:.3f} ms")
     assert sorted(took)[5] <= 2e-3
+
+
+# ---------------------------------------------------------------------------
+# workspaces
+# ---------------------------------------------------------------------------
+def test_only_users_of_expansions_carry_their_buffers():
+    """Device memory of an evaluation of 12,288 water atoms: BF16, whose nets
+    have no expansion, takes 6 KB an atom less than FP16, whose nets have (of
+    the same layout otherwise)."""
+    w = synth.workload("water12288")
+    took = {}
+    for prec in ("bf16", "fp16"):
+        m = _model(w["spec"], prec)
+        x, t = torch.tensor(w["coords"], device="cuda"), torch.tensor(w["types"], device="cuda")
+        m.compute(x[:192], t[:192], w["box"])  # what is not the workspace
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        m.compute(x, t, w["box"])
+        torch.cuda.synchronize()
+        took[prec] = free - torch.cuda.mem_get_info()[0]
+        del m
+    say(f"[routes] workspace bf16 {took['bf16'] / 2**20:.0f} MiB, fp16 {took['fp16'] / 2**20:.0f} MiB")
+    assert took["fp16"] - took["bf16"] >= 5000 * 12288
+
+
+def test_noalloc_route_is_the_calls_own():
+    """No-allocation calls: a system too large to have the expansions' buffers
+    beside its own leaves none of its route to the small one after it, whose
+    energy is bit for bit that of a context's first call.  FP16, where the two
+    routes differ in digits that a sum of energies shows (bars of the FP16 tests:
+    2^-14 of the energy, force RMSE 1e-3 eV/A)."""
+    from paper_2005_00223_amd import _lib as L
+
+    def run(ctx, x, t, box):
+        xd, td = torch.tensor(x, device="cuda"), torch.tensor(t, device="cuda")
+        e, f, v = (torch.zeros(k, dtype=torch.float64, device="cuda") for k in (1, 3 * len(x), 9))
+        L.dp_compute_noalloc(ctx, len(x), xd.data_ptr(), td.data_ptr(), [box[0], 0, 0, 0, box[1], 0, 0, 0, box[2]],
+                             e.data_ptr(), f.data_ptr(), v.data_ptr())
+        torch.cuda.synchronize()
+        return e.item(), f.cpu().numpy().reshape(-1, 3)
+
+    small = synth.workload("water192")
+    blob = synth.pack_blob(small["spec"])
+    bx, bt, bbox = synth.water_system(19, 19 * 3.105, 0.1, seed=6)
+    out = []
+    for first in (None, (bx, bt, bbox)):
+        ctx = L.dp_create(0, torch.cuda.current_stream().cuda_stream)
+        L.dp_set_model(ctx, blob, L.PRECISION["fp16"])
+        if first:
+            eb, fb = run(ctx, *first)
+            m = _model(small["spec"], "fp16")
+            e0, f0, _ = m.compute(*first)
+            rmse = np.sqrt(((fb - f0.cpu().numpy()) ** 2).sum(1).mean())
+            say(f"[routes] noalloc {len(bt)} atoms: E {abs(eb / float(e0) - 1):.1e}, F RMSE {rmse:.1e}")
+            assert 0.0 < abs(eb / float(e0) - 1) <= 2.0 ** -14 and rmse <= 1e-3
+        out.append(run(ctx, small["coords"], small["types"], small["box"]))
+        L.dp_destroy(ctx)
+    (e1, f1), (e2, f2) = out
+    say(f"[routes] noalloc water192 first / after the large one: E {abs(e1 - e2):.1e}, F {np.abs(f1 - f2).max():.1e}")
+    assert e1 == e2 and np.abs(f1 - f2).max() <= 1e-12
