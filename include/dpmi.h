@@ -66,13 +66,22 @@ enum {
  *   hi + lo 16-bit pairs (about 22 bits); tanh, the descriptor contractions,
  *   the remaining fitting layers and the output layer in FP32.
  * An embedding net is a function of the one number s: under DP_FP64,
- * DP_MIX_FP32 and DP_MIX_FP16 (embedding widths up to 128) dp_set_model lays
- * the nets out as piecewise Chebyshev expansions, from the weights as the
- * policy rounds them and below the rounding of its arithmetic (double under
- * DP_FP64, FP32 otherwise), and evaluations sum those; the layers themselves
- * are evaluated where a net has no such expansion, in frames with a pair
- * closer than about 0.03 A (that evaluation then costs both), under
- * DP_MIX_BF16, for wide nets and for the 16-bit student nets.
+ * DP_MIX_FP32 and DP_MIX_FP16 (embedding widths up to 128) dp_set_model and
+ * dp_set_precision lay the nets out, once per precision, as piecewise
+ * Chebyshev expansions, from the weights as the policy rounds them and to the
+ * rounding of its arithmetic (double under DP_FP64, FP32 otherwise), and
+ * evaluations sum those.  The layers themselves are evaluated
+ *   - under DP_MIX_BF16, for wide nets and for the 16-bit student nets;
+ *   - where the nets have no expansion: nets so rough, or of so many atom
+ *     types, that an atom's neighbours beyond 1 A would lie in more than 8
+ *     pieces (seeded nets: four types and more in double, eight in FP32);
+ *   - in frames with a pair beyond the expansions' range, s = 32 (0.03 A)
+ *     where the nets allow, never less than s = 2 (0.5 A; three seeded types in
+ *     double: s = 13), or with an atom whose neighbours lie in more than 12
+ *     pieces.  Such an evaluation costs both; dp_md_run goes on by the layers
+ *     until its next check (thermo_every) and then tries the expansions again;
+ *   - where there is no device memory, or no room in the static scratch of
+ *     dp_compute_noalloc, for the expansions' buffers.
  * Coordinates, wrapping, distances, the environment matrix (before its
  * rounding), the force Jacobian, energy / force / virial sums and the
  * integrator stay double in every mode. */
@@ -258,8 +267,9 @@ int dp_set_wide_storage(dp_ctx *c, int mode);
  * error arose (coords at that step, vel before its second half kick).  A
  * skin candidate list too small for the local density is then doubled (up
  * to four times per call) and the run resumes at that step, giving the
- * same trajectory as a large enough list from the start; other errors
- * return with coords and vel in that stopped state. */
+ * same trajectory as a large enough list from the start, and so does a run
+ * that met a pair beyond the expansions (see the precision policies); other
+ * errors return with coords and vel in that stopped state. */
 int dp_md_run(dp_ctx *c, int64_t natoms, double *coords, double *vel, const int32_t *types, const double *box,
               const double *masses, double dt, double skin, int64_t nsteps, int64_t thermo_every,
               double *thermo, double *forces);

@@ -2413,10 +2413,11 @@ int dp_md_run(dp_ctx *c, int64_t n, double *coords, double *vel, const int32_t *
   rc = start(0);
   if (rc) return rc;
   int regrown = 0;
+  int64_t layer_checks = 0, back_checks = 0;
   // Read the flags after step st.  A skin-list overflow at a step after the
   // last check stopped the integrator there: the list is grown and the run
   // restarted at that step (*resume), and so is a run that met a pair beyond
-  // the expansions, on the layers; other errors end the run.
+  // the expansions, on the layers for a while; other errors end the run.
   auto check = [&](int64_t st, int64_t &resume) -> int {
     HIPCHK(c, hipGetLastError());
     int r = read_status(c);
@@ -2430,9 +2431,13 @@ int dp_md_run(dp_ctx *c, int64_t n, double *coords, double *vel, const int32_t *
       const long long f0 = nsteps == 0 ? 0 : c->h_status->fault_step;
       if (((fl & FLAG_CAND_CAP) && regrown >= 4) || f0 < 0 || f0 > st)
         return fail(c, DP_E_CAP, "skin candidate list overflow; use a smaller skin");
-      // a pair came closer than the expansions reach: the rest of the run
-      // evaluates the layers
-      if (fl & FLAG_FAR) c->exp_off = true;
+      // a pair came closer than the expansions reach: the layers until a check
+      // has passed, then the expansions again; after a run of failed returns
+      // twice as many checks each time
+      if (fl & FLAG_FAR) {
+        c->exp_off = true;
+        layer_checks = back_checks = std::max<int64_t>(1, 2 * back_checks);
+      }
       if (fl & FLAG_CAND_CAP) {
         ++regrown;
         r = ensure_ws(c, n, ncell, 2 * c->ws.cand_cap);
@@ -2441,6 +2446,10 @@ int dp_md_run(dp_ctx *c, int64_t n, double *coords, double *vel, const int32_t *
       r = start((int64_t)f0);
       if (r) return r;
       resume = (int64_t)f0;
+    } else if (!c->exp_off) {
+      back_checks = 0;  // the steps since the last check ran on the expansions
+    } else if (--layer_checks <= 0) {
+      c->exp_off = false;
     }
     return DP_OK;
   };

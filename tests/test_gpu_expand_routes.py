@@ -386,3 +386,52 @@ def test_noalloc_route_is_the_calls_own():
     (e1, f1), (e2, f2) = out
     say(f"[routes] noalloc water192 first / after the large one: E {abs(e1 - e2):.1e}, F {np.abs(f1 - f2).max():.1e}")
     assert e1 == e2 and np.abs(f1 - f2).max() <= 1e-12
+
+
+# ---------------------------------------------------------------------------
+# MD: from the layers back to the expansions
+# ---------------------------------------------------------------------------
+def test_md_returns_to_the_expansions():
+    """Two pairs meet in turn, at steps 7 and 15 (checks every 4 steps): each
+    restarts the run, so between them it was back on the expansions.  Step 8
+    and step 16 count twice; the trajectory is the oracle's."""
+    from oracle import oracle as O
+    spec = synth.copper_model(1)
+    x = np.array([[9.0, 9.0, 9.0], [9.69, 9.005, 9.0], [13.0, 10.0, 8.0], [30.0, 9.0, 9.0], [31.5, 9.005, 9.0]])
+    v = np.array([[0.2, 0.0, 0.0], [-0.2, 0.0, 0.0], [0.0, 0.0, 0.0], [0.2, 0.0, 0.0], [-0.2, 0.0, 0.0]])
+    t, box, nst = np.zeros(5, dtype=np.int32), np.array([44.0, 21.0, 21.0]), 20
+    ora = O.Oracle(synth.pack_blob(spec))
+    near = []
+    for k in range(nst + 1):
+        y = ora.verlet(x, v, t, box, [63.546], 0.25, k, every=0)[0]
+        near.append(min(np.linalg.norm(y[0] - y[1]), np.linalg.norm(y[3] - y[4])))
+    assert [k for k in range(nst + 1) if near[k] < 1.0 / 32.0] == [7, 15]
+    xo, vo, tho = ora.verlet(x, v, t, box, [63.546], 0.25, nst, every=4)
+    m = _model(spec, "fp64")
+    xg, vg = torch.tensor(x, device="cuda"), torch.tensor(v, device="cuda")
+    th = m.md_run(xg, vg, t, box, [63.546], 0.25, nst, skin=1.0, thermo_every=4).cpu().numpy()
+    dx, dv, ev = np.abs(xg.cpu().numpy() - xo).max(), np.abs(vg.cpu().numpy() - vo).max(), m.stats()["evaluations"]
+    say(f"[routes] MD, two meetings: x {dx:.2e}, v {dv:.2e}, {ev} evaluations")
+    assert ev == nst + 2
+    assert dx <= 1e-7 and dv <= 1e-7 * max(1.0, np.abs(vo).max())
+    assert np.abs(th[:, 1:5] - tho[:, 1:5]).max() <= 1e-6 * np.abs(tho[:, 1:5]).max()
+
+
+@pytest.mark.parametrize("thermo", [1, 3])
+def test_md_of_a_pair_that_stays_beyond_the_range(thermo):
+    """A pair that stays at 0.016 A: the returns to the expansions fail, ever
+    more rarely, and the run goes on by the layers."""
+    from oracle import oracle as O
+    spec = synth.copper_model(1)
+    x = np.array([[9.0, 9.0, 9.0], [9.015, 9.0, 9.005], [13.0, 10.0, 8.0]])
+    t, box, nst = np.zeros(3, dtype=np.int32), np.full(3, 21.0), 24
+    ora = O.Oracle(synth.pack_blob(spec))
+    xo, vo, tho = ora.verlet(x, 0 * x, t, box, [63.546], 0.002, nst, every=thermo)
+    assert np.linalg.norm(xo[0] - xo[1]) < 1.0 / 32.0
+    m = _model(spec, "fp64")
+    xg, vg = (torch.tensor(a, device="cuda") for a in (x, 0 * x))
+    th = m.md_run(xg, vg, t, box, [63.546], 0.002, nst, skin=1.0, thermo_every=thermo).cpu().numpy()
+    dx = np.abs(xg.cpu().numpy() - xo).max()
+    say(f"[routes] MD at 0.016 A: x {dx:.2e}, {m.stats()['evaluations']} evaluations")
+    assert dx <= 1e-9
+    assert np.abs(th[:, 1:5] - tho[:, 1:5]).max() <= 1e-8 * np.abs(tho[:, 1:5]).max()
