@@ -435,3 +435,105 @@ def test_md_of_a_pair_that_stays_beyond_the_range(thermo):
     say(f"[routes] MD at 0.016 A: x {dx:.2e}, {m.stats()['evaluations']} evaluations")
     assert dx <= 1e-9
     assert np.abs(th[:, 1:5] - tho[:, 1:5]).max() <= 1e-8 * np.abs(tho[:, 1:5]).max()
+
+
+# ---------------------------------------------------------------------------
+# expansions in company they had not been seen in
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("reps", [(1, 1, 1), (5, 5, 1)])
+@pytest.mark.parametrize("fit,M2", [((40,), 16), ((120, 240), 16), ((24, 24, 24), 5), ((272, 272), 16)])
+def test_layer_fitting_nets_behind_expansions(fit, M2, reps, prec):
+    """Fitting nets the fused kernels do not take (a width that is not a
+    multiple of 16 or above 256, a doubling skip): D and dE/dD in memory between
+    the expansions and the layer GEMMs."""
+    spec = synth.random_model(2, 4.5, 2.0, (64, 64), M2=M2, fit=fit, seed=22, out_scale=-8.0, desc_norm=2.0)
+    x, t, box = _cell()
+    r = _oracle(spec, x, t, box, prec)
+    X, T, B, copies, order = _repeat(x, t, box, reps)
+    say(f"[routes] fitting {fit}, M2 {M2}, {prec}: {len(X)} atoms")
+    _compare(_model(spec, prec).compute(X, T, B), r, prec, f"{fit}", copies, order)
+
+
+@pytest.mark.parametrize("ntypes,prec", [(3, "fp64"), (4, "fp64"), (4, "fp32"), (6, "fp32"), (8, "fp32")])
+@pytest.mark.parametrize("reps", [(1, 1, 1), (5, 5, 1)])
+def test_many_types(ntypes, prec, reps):
+    """Three types in double, four and six in float on expansions (tests of the
+    tables say which have them), four in double and eight in float by the layers."""
+    spec = synth.random_model(ntypes, 4.5, 2.0, (32,) * ntypes, seed=5, out_scale=-8.0, desc_norm=2.0)
+    x, t, box = _cell(ntypes)
+    r = _oracle(spec, x, t, box, prec)
+    X, T, B, copies, order = _repeat(x, t, box, reps)
+    say(f"[routes] {ntypes} types, {prec}: {len(X)} atoms")
+    _compare(_model(spec, prec).compute(X, T, B), r, prec, f"{ntypes} types", copies, order)
+
+
+# bars of the FP16 tests' kernel arithmetic, against the oracle on the weights
+# the kernels hold: 2^-14, here of the largest force and virial component and of
+# the summed |E_i|
+FP16_BAR = 2.0 ** -14
+
+
+@pytest.mark.parametrize("order", ["lattice", "shuffled"])
+def test_merged_scatter_fp16(order):
+    """4,000 atoms in FP16, forces merged in LDS: copies of a cell of 500."""
+    from oracle import oracle as O
+    from oracle import student as S
+    x, t, box = synth.fcc_copper(5, 3.634, 0.1, seed=4)
+    spec = synth.copper_model(1)
+    r = O.Oracle(synth.pack_blob(S.round_spec16(spec, 0))).eval(x, t, box)
+    X, T, B, copies, p = _repeat(x, t, box, (4, 2, 1), seed=1)
+    if order == "lattice":
+        back = np.argsort(p)
+        X, T, p = X[back], T[back], np.arange(len(p))
+    e, f, v = _model(spec, "fp16").compute(X, T, B)
+    want = np.tile(r["force"], (copies, 1))[p]
+    df = np.abs(f.cpu().numpy() - want).max() / np.abs(want).max()
+    de = abs(float(e) / copies - r["energy"]) / np.abs(r["atom_e"]).sum()
+    dv = np.abs(v.cpu().numpy() / copies - r["virial"]).max() / np.abs(r["virial"]).max()
+    say(f"[routes] merged scatter fp16 {order}: F {df:.2e}, E {de:.2e}, V {dv:.2e}")
+    assert max(df, de, dv) <= FP16_BAR
+
+
+@pytest.mark.parametrize("count", [1, 15, 16, 17, 63, 64, 65, 127, 129, 200])
+def test_neighbour_counts_fp16(count):
+    """A cluster of count + 1 atoms, every one the others' neighbour, several
+    pieces in each list; a first fitting layer scaled down so that its tanh does
+    not saturate (1 - t^2 of a saturated one loses the digits that this test
+    looks at).  Forces and energy; the virial of a cluster is a small difference."""
+    from oracle import oracle as O
+    from oracle import student as S
+    spec = synth.random_model(1, 7.0, 3.0, (256,), seed=6, out_scale=-20.0, desc_norm=8.0 + count / 2.0)
+    spec.fit_W[0][0] = spec.fit_W[0][0] * 0.1
+    rng = np.random.default_rng(count)
+    g = np.stack(np.meshgrid(*[np.arange(6)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    g = g[np.argsort(((g - 2.5) ** 2).sum(1), kind="stable")][:count + 1]
+    x = 0.85 * g + rng.uniform(-0.1, 0.1, size=g.shape) + 8.0
+    t, box = np.zeros(count + 1, dtype=np.int32), np.full(3, 22.0)
+    r = O.Oracle(synth.pack_blob(S.round_spec16(spec, 0))).eval(x, t, box)
+    e, f, _ = _model(spec, "fp16").compute(x, t, box)
+    df = np.abs(f.cpu().numpy() - r["force"]).max() / np.abs(r["force"]).max()
+    de = abs(float(e) - r["energy"]) / np.abs(r["atom_e"]).sum()
+    say(f"[routes] fp16 cluster of {count + 1}: F {df:.2e}, E {de:.2e}")
+    assert max(df, de) <= FP16_BAR
+
+
+def test_judge_meets_a_far_pair():
+    """FP16: the student's layers take a pair at 0.02 A, the judging teacher's
+    expansions do not; the run starts again on the layers and the RMSE is that
+    of the two nets' own evaluations (1e-6 relative: atomics' order)."""
+    x, t, box = _frame("pair")
+    spec = synth.copper_model(1)
+    m = _model(spec, "fp16")
+    m.student_set_model(synth.pack_blob(synth.student_spec(spec, synth.random_student_params(spec, 31))))
+    m.student_table(False)
+    _, ft, _ = m.compute(x, t, box)
+    m.student_use(True)
+    _, fs, _ = m.compute(x, t, box)
+    expect = float(((fs - ft) ** 2).sum(1).mean().sqrt())
+    m.student_judge(20, 1e9)
+    xg = torch.tensor(x, device="cuda")
+    m.md_run(xg, torch.zeros_like(xg), t, box, [63.546], 1e-3, 0, skin=0.5, thermo_every=1)
+    st = m.stats()
+    say(f"[routes] judge with a far pair: RMSE {st['last_judge_rmse']:.9e}, expected {expect:.9e}")
+    assert abs(st["last_judge_rmse"] - expect) <= 1e-6 * expect and st["teacher_fallbacks"] == 0
