@@ -193,10 +193,12 @@ bool fit_pieces(const std::vector<NetT> &nets, int M1p, double tol, std::vector<
     node[k] = std::cos(pi * ((F)k + F(0.5)) / J);
     for (int j = 0; j < J; ++j) ct[k][j] = std::cos(pi * (F)k * ((F)j + F(0.5)) / J) * (k == 0 ? F(1) : F(2)) / J;
   }
-  // as many threads as have 0.3 ms of work each: starting one takes some 0.03 ms
+  // as many threads as have a millisecond of work each, four at most: a caller's
+  // own threads may be spinning on the same CPUs (eight, from 0.3 ms, took a
+  // water model's FP16 load from 26 to 35 ms just after a numpy least squares)
   double ns = 0.0;
   for (auto &p : pieces) ns += nets[p.net].ns(sizeof(F) > sizeof(double)) * J;
-  const size_t nth = (size_t)std::min(8.0, 1.0 + ns / 3e5);
+  const size_t nth = (size_t)std::min(4.0, 1.0 + ns / 1e6);
   return parallel_for(pieces.size(), nth, [&](size_t q) {
     Piece &p = pieces[q];
     Buffers<F> u;
