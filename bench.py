@@ -105,8 +105,10 @@ PHASE_KERNEL = {
     ("env", False): ("k_env<HIP_vector_type<float, 4u> >", "k_env"),
 }
 HASH_FILES = {"k_embed_mix": ("k_embed_mix.hip", "dp_mix.h", "dp_internal.h"),
-              "k_fit_mix": ("k_fit_mix.hip", "dp_mix.h", "dp_internal.h"),
-              "k_nlist": ("k_nlist.hip", "dp_internal.h"), "k_env": ("k_env.hip", "dp_internal.h")}
+              "k_fit_mix": ("k_fit_mix.hip", "dp_mix.h", "dp_fit_fused.h", "dp_internal.h"),
+              "k_nlist": ("k_nlist.hip", "dp_internal.h"), "k_env": ("k_env.hip", "dp_internal.h"),
+              "k_embed_exp": ("k_embed_exp.hip", "dp_expand.h", "dp_f64.h", "dp_internal.h"),
+              "k_fit_fused": ("k_fit_fused.hip", "dp_fit_fused.h", "dp_f64.h", "dp_internal.h")}
 PMC_FILE = os.path.join(HERE, "profiles", "cu500k_fp16_student_pmc.txt")
 
 
@@ -234,6 +236,7 @@ def profile_summary(kind, root, command):
         f = glob.glob(os.path.join(root, "**", "*kernel_stats.csv"), recursive=True)[0]
         rows = list(csv.DictReader(open(f)))
         out.append(f"# condensed from {os.path.basename(f)} by bench.py --profile-summary kernels")
+        out += [f"# source-hash {g}: {source_hash(g)}" for g in HASH_FILES]
         out.append("%-62s %6s %10s %10s %6s" % ("kernel", "calls", "avg_ms", "total_ms", "pct"))
         for r in rows:
             out.append("%-62s %6s %10.4f %10.3f %6.2f" % (r["Name"].split("(")[0].replace("void ", "")[:62], r["Calls"],
@@ -267,8 +270,7 @@ def profile_summary(kind, root, command):
                    "reads FETCH_SIZE = 1/2 and WRITE_SIZE = 1 x its bytes on this GPU)")
     out.append("# hbm_GB = (FETCH_SIZE * fetch factor + WRITE_SIZE * write factor) * 1024 / 1e9, per dispatch;"
                " mfma_busy, valu_active, lds_active are fractions of the kernel's SIMD-cycles")
-    for g in HASH_FILES:
-        out.append(f"# source-hash {g}: {source_hash(g)}")
+    out += [f"# source-hash {g}: {source_hash(g)}" for g in HASH_FILES]
     out.append("%-50s %5s %9s %9s %11s %10s %8s %11s %11s %8s" % (
         "kernel", "disp", "ms", "mfma_busy", "valu_active", "lds_active", "bank/lds", "FETCH_KiB", "WRITE_KiB",
         "hbm_GB"))

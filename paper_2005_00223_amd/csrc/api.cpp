@@ -825,9 +825,11 @@ int upload_exp_t(dp_ctx *c, const ExpTables &t, int ntypes, EmbNets::Exp &e) {
 // weights its layer kernels hold.  Nets without one leave ok false.
 int upload_exp(dp_ctx *c, const HostModel &m, EmbNets &en, int precision) {
   const int kind = exp_kind(precision);
-  // BF16, wide nets and the 16-bit student nets keep their layer kernels:
-  // their results carry those kernels' own rounding (5e-5 and 1e-4 of the
-  // forces on copper), and callers' trajectories with it
+  // BF16, wide nets and the 16-bit student nets keep their layer kernels, by
+  // choice: expansions would take their results from those kernels' 16-bit
+  // operands to FP32 (BF16 by 5e-5, wide nets by 1e-4 of the forces on copper,
+  // below the layers' own error against 64 bits), and callers' trajectories with
+  // them
   const Dims &d = en.d;
   if (kind < 0 || en.exp[kind].built) return DP_OK;
   if (precision == DP_MIX_FP16 && (mix_shape_id(d) < 0 || &en == &c->en[1])) return DP_OK;
