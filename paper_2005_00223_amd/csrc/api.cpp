@@ -193,7 +193,7 @@ struct Workspace {
   void *exp_hm = nullptr;
   int seg = 0;
   bool env_ok = false;  // the environment rows are those of the current lists
-  bool exp_none = false; // laid out without exp_hm: no device memory for it
+  bool exp_none = false;  // laid out without exp_hm: no device memory for it
   int prec = -1;  // precision the buffers were laid out for
   DevStatus *status;
 };
@@ -1061,7 +1061,9 @@ inline bool use_exp(const dp_ctx *c) {
 }
 
 // ... and its fitting net in the fused kernels (no D, dE/dT in place of dE/dD)
-inline bool use_fused(const dp_ctx *c) { return c->exp_now && !prec16(c->precision) && c->d_fit_pack[c->precision == DP_FP64 ? 0 : 1]; }
+inline bool use_fused(const dp_ctx *c) {
+  return c->exp_now && !prec16(c->precision) && c->d_fit_pack[c->precision == DP_FP64 ? 0 : 1];
+}
 
 template <typename Real>
 FitFusedArgs<Real> fused_args(dp_ctx *c, int64_t rows) {

@@ -335,8 +335,10 @@ def test_only_users_of_expansions_carry_their_buffers():
     """Device memory of an evaluation of 12,288 water atoms: BF16, whose nets
     have no expansion, takes 6 KB an atom less than FP16, whose nets have (of
     the same layout otherwise)."""
+    import gc
     w = synth.workload("water12288")
     took = {}
+    gc.collect()  # no context of an earlier test is freed in between
     for prec in ("bf16", "fp16"):
         m = _model(w["spec"], prec)
         x, t = torch.tensor(w["coords"], device="cuda"), torch.tensor(w["types"], device="cuda")
